@@ -158,7 +158,8 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
     s_ell[t] = ell;
     s_cnt[t] = direct;
     uint32_t n_rows;
-    s_rbase[t] = block_exclusive_sum<kBlock>(rows, s_tmp, &n_rows);   // contains barriers
+    s_rbase[t] = block_exclusive_sum<kBlock>(rows, s_tmp, &n_rows);
+    __syncthreads();                                  // the search below reads every thread's s_rbase
     for (uint32_t row0 = 0; row0 < n_rows; row0 += kBlock) {
         const uint32_t rho = row0 + (uint32_t)t;
         if (rho < n_rows) {

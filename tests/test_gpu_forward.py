@@ -626,3 +626,44 @@ def test_active_ratio_and_activation_iou(ctx):
     assert 0.0 < iou < 1.0
     print(f"active ratio at t=0.5: {ratio:.4f} (oracle {s1.sum() / n:.4f}..{m1.sum() / n:.4f}); "
           f"IoU(0.3, 0.5) {iou:.4f}")
+
+
+def test_fresh_states_beside_other_streams_match_one_stream(ctx):
+    """Views rendered into new states on three contexts (a stream each), beside
+    the adjoints of earlier views, give the images and tile lists of one
+    stream.  The first touch of new buffers delays the wavefronts of a
+    preprocess workgroup unevenly: without a barrier between writing and
+    searching the workgroup's row offsets it miscounted a few tiles there."""
+    from paper_2503_16422_amd.render import Context, GaussianModel
+    model = GaussianModel.from_scene(inputs.dense_scene(300_000, seed=3), "cuda:0")
+    cams = inputs.arc_cameras(20, 4.0, 1352, 1014)
+    views = [(cams[5], 0.6), (cams[14], 0.73), (cams[2], 0.19), (cams[4], 0.055)]
+    cfg = _lib.default_cfg(tile_w=32, tile_h=32, batch=256)
+    ref, n_ref = [], []
+    for cam, t in views:
+        rgb, _, st = ctx.render(model, cam, t, cfg, keep_state=True)
+        ref.append(rgb)
+        n_ref.append(ctx.binning(st)["n_inst"])
+        st.release()
+    ctxs = [Context(0) for _ in range(3)]
+    streams = [torch.cuda.Stream() for _ in ctxs]
+    dL = torch.ones_like(ref[0])
+    torch.cuda.synchronize()
+    for _ in range(4):
+        states, got = [], []
+        for v, (cam, t) in enumerate(views):
+            c = ctxs[v % 3]
+            with torch.cuda.stream(streams[v % 3]):
+                rgb, _, st = c.render(model, cam, t, cfg, keep_state=True)
+                c.backward_2d(st, dL)
+            states.append(st)
+            got.append(rgb)
+        torch.cuda.synchronize()
+        n_got = [st.ctx.binning(st)["n_inst"] for st in states]
+        for st in states:
+            st.release()
+        assert n_got == n_ref
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b)
+    for c in ctxs:
+        c.close()
