@@ -130,3 +130,52 @@ def test_backward_rejects_quantised_model(ctx):
     with pytest.raises(_lib.FdgsError):
         ctx.backward(st, torch.ones_like(rgb), q)
     ctx.release(st)
+
+
+def chain_distances(x, c):
+    """The distance that decides: float32 t = x - c, acc = fma(t, t, acc) in component order.  The
+    square and the sum are formed in float64 and rounded once more, which can differ from a fused
+    operation by one unit in the last place."""
+    x, c = x.astype(np.float32), c.astype(np.float32)
+    acc = np.zeros((x.shape[0], c.shape[0]), np.float32)
+    with np.errstate(over="ignore", invalid="ignore"):
+        for d in range(x.shape[1]):
+            t = (x[:, None, d] - c[None, :, d]).astype(np.float64)
+            acc = (t * t + acc.astype(np.float64)).astype(np.float32)
+    return acc
+
+
+@pytest.mark.parametrize("n,k", [(1, 1), (31, 2), (65, 31), (257, 33), (700, 64), (1030, 97), (2500, 300)])
+@pytest.mark.parametrize("kind", ["plain", "twins", "extreme"])
+def test_assignment_is_the_nearest_in_float32(ctx, n, k, kind):
+    """The screened assignment is the float32 search's, at the edges of its tiles (32 entries, 64 and
+    256 Gaussians, splits of the entries), with equal entries (the lower one wins) and with
+    vectors of extreme size, infinities and NaN (no finite distance: entry 0).  Tolerance: one
+    float32 unit, by which the reference's twice rounded sums may differ from fused ones."""
+    sc = inputs.tiny_scene(max(n, k), seed=n + k)
+    rng = np.random.default_rng(n * 1000 + k)
+    if kind == "twins":
+        sc.sh[..., :] = sc.sh[..., rng.integers(0, max(1, min(n, 5)), max(n, k))]
+    if kind == "extreme":
+        scale = 10.0 ** rng.integers(-30, 19, max(n, k))
+        sc.sh *= scale.astype(np.float32)
+        for v, i in ((np.inf, 0), (np.nan, 1), (-np.inf, 2)):
+            if n > 40 * (i + 1):
+                sc.sh[i, 1, rng.integers(0, n, 2)] = v
+    model = model_of(sc)
+    init = torch.from_numpy(rng.permutation(max(n, k))[:k].astype(np.int32)).cuda()
+    code, assign = ctx.sh_kmeans(model, k, 0, init_index=init)
+    torch.cuda.synchronize()
+    d = chain_distances(vq.sh_vectors(sc.sh), code.cpu().numpy())
+    a = assign.cpu().numpy()
+    d = np.where(np.isnan(d), np.float32(np.inf), d)
+    low = d.min(axis=1)
+    got = d[np.arange(d.shape[0]), a]
+    assert np.all(got <= np.nextafter(low, np.float32(np.inf)))
+    clear = (d <= np.nextafter(np.nextafter(low, np.float32(np.inf)), np.float32(np.inf))[:, None]).sum(1) == 1
+    ref = np.where(np.isinf(low), 0, d.argmin(axis=1))
+    same = clear | np.isinf(low) | (d == low[:, None]).all(axis=1)
+    assert np.array_equal(a[same], ref[same])
+    if kind == "twins":
+        c = code.cpu().numpy()                     # equal entries: always the lowest of them
+        assert all(not (c[:a[i]] == c[a[i]]).all(axis=1).any() for i in range(a.size))
