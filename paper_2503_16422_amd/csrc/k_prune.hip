@@ -17,6 +17,10 @@ constexpr int kBlock = 256;
 // Per Gaussian: S^TV = sum_t 1 / (0.5 tanh|p''(t)| + 0.5) with
 // p''(t) = ((t - mu_t)^2 / S44^2 - 1 / S44) p(t) (float64), and the volume
 // exp(sum of log scales) as a float32 sort key (0 for invalid Gaussians).
+// Bound by float64 instructions (a thread's 300 terms against 68 B of
+// parameters).  With tanh a = (1 - e) / (1 + e), e = exp(-2 a), a term is
+// 1 + exp(-2 |p''|): two exponentials and no division, where tanh and the
+// quotients took 2.00 ms for 1M Gaussians x 300 times (now 0.49 ms).
 __global__ void __launch_bounds__(kBlock) temporal_volume_kernel(KModel m, const double *times, int32_t n_times,
                                                                  float *tv, uint32_t *vol_key, uint32_t *vals) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -26,12 +30,13 @@ __global__ void __launch_bounds__(kBlock) temporal_volume_kernel(KModel m, const
     uint32_t key = 0u;
     if (load_gaussian(m, i, G)) {
         const double s44 = sigma44_of(G);
+        const double i0 = -1.0 / (2.0 * s44), i1 = 1.0 / s44, i2 = 1.0 / (s44 * s44);
         double acc = 0.0;
+#pragma unroll 2
         for (int f = 0; f < n_times; ++f) {
             const double d = times[f] - G.mu[3];
-            const double p = exp(-d * d / (2.0 * s44));
-            const double p2 = (d * d / (s44 * s44) - 1.0 / s44) * p;
-            acc += 1.0 / (0.5 * tanh(fabs(p2)) + 0.5);
+            const double p2 = (d * d * i2 - i1) * exp(d * d * i0);
+            acc += 1.0 + exp(-2.0 * fabs(p2));
         }
         s = (float)acc;
         const float vol = (float)exp(G.ls[0] + G.ls[1] + G.ls[2] + G.ls[3]);
