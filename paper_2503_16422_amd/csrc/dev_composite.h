@@ -92,13 +92,20 @@ struct Cells {
 };
 
 // Bit w set when the record's footprint ellipse reaches a pixel of wavefront
-// w's cell of the tile with origin (x0, y0) (every bit when tile culling is
-// off, or the ellipse is not usable for it).  One column span per band of
-// cell rows, then a range test per cell of the band.
+// w's cell of the tile with origin (x0, y0) (every bit when the ellipse is not
+// usable for it).  One column span per band of cell rows, then a range test
+// per cell of the band.  The ellipse is that of the alpha test, whatever the
+// lists were made from: a list that holds more (tile or opacity culling off)
+// gives the same image, and its records that cannot reach alpha_min anywhere
+// are passed over here once per tile instead of once per pixel (unfiltered
+// frame of 3M Gaussians, 16x16 tiles: compositor 1984 -> 334 us).
 template <int TW, int TH, int PPT>
-__device__ __forceinline__ uint32_t reached_cells(const Rec2D &r, const RenderParams &rp, int x0, int y0) {
+__device__ __forceinline__ uint32_t reached_cells(const Rec2D &r, RenderParams rp, int x0, int y0) {
     using C = Cells<TW, TH, PPT>;
+    rp.tile_cull = 1;
+    rp.temporal_cull = 1;
     const CullEllipse e = cull_ellipse(r, rp);
+    if (e.a > 0.0f && r.b.w < rp.alpha_min * (1.0f - 1e-4f)) return 0u;   // far more than alpha's rounding
     uint32_t m = 0;
 #pragma unroll 1
     for (int band = 0; band < C::NW / C::CX; ++band) {

@@ -65,7 +65,6 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
     // branching per pixel)
     constexpr bool kBits = C::NW > 1;
     constexpr bool kBranchy = PPT == 1 && !kBits;
-    const bool cull = a.rp.tile_cull != 0;   // without tile culling every record reaches every cell
     constexpr int kWords = BATCH / 64;
     __shared__ uint64_t s_bits[kBits ? C::NW * kWords : 1];
     const int n_tiles = a.rp.tiles_x * a.rp.tiles_y;
@@ -127,14 +126,12 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                 const uint32_t id = a.ids[base + k];
                 const Rec2D r = a.rec[id];
                 const ExpRec q = stage_exp(r, ox, oy);
-                if constexpr (kBits) {
-                    if (cull) cells = reached_cells<TW, TH, PPT>(r, a.rp, tx * TW, ty * TH);
-                }
+                if constexpr (kBits) cells = reached_cells<TW, TH, PPT>(r, a.rp, tx * TW, ty * TH);
                 s_rec[3 * k] = make_float4(q.gx, q.s, q.c0, q.kx);
                 s_rec[3 * k + 1] = make_float4(q.lo, q.q, r.c.x, r.c.y);
                 s_rec[3 * k + 2] = make_float4(r.c.z, __uint_as_float(id), 0.0f, 0.0f);
             }
-            if (kBits && cull) {
+            if constexpr (kBits) {
                 const int word = k0 / 64 + wave;
 #pragma unroll
                 for (int w = 0; w < C::NW; ++w) {
@@ -255,7 +252,7 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                 for (int p = 0; p < PPT; ++p) left = left || thr[p] < kInf;
                 return __ballot(left) != 0ull;
             };
-            if (kBits && cull) {
+            if constexpr (kBits) {
                 // only the records whose ellipse reaches this wavefront's cell, in
                 // order; the liveness test every 8 of them
                 int since = 0;

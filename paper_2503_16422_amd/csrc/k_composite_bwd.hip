@@ -49,8 +49,8 @@ struct BwdArgs {
 // record in the even lanes and the second in the odd ones, then three DPP
 // steps that keep a lane's parity -- and added into the tile's LDS
 // accumulators by two lanes per row; one global add per value and Gaussian
-// leaves the tile after each batch.  With several cells per tile (and tile
-// culling on) a wavefront walks only the records whose footprint ellipse
+// leaves the tile after each batch.  With several cells per tile
+// a wavefront walks only the records whose footprint ellipse
 // reaches its cell: the others have alpha below alpha_min at every one of its
 // pixels and contribute nothing.
 template <int CTRL>
@@ -67,7 +67,6 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
     constexpr bool kBits = C::NW > 1;
     constexpr int kWords = BATCH / 64;
     __shared__ uint64_t s_bits[kBits ? C::NW * kWords : 1];
-    const bool cull = a.rp.tile_cull != 0;
     // per staged record three float4: gx, q s, c0, kx | log2 opacity, q, r, g | b, gy, opacity, id
     __shared__ float4 s_rec[3 * BATCH];
     __shared__ float s_acc[BATCH * kVals];   // per-Gaussian sums of the tile
@@ -130,11 +129,9 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
                 s_rec[3 * k] = make_float4(q.gx, q.s, q.c0, q.kx);
                 s_rec[3 * k + 1] = make_float4(q.lo, q.q, r.c.x, r.c.y);
                 s_rec[3 * k + 2] = make_float4(r.c.z, q.gy, r.b.w, __uint_as_float(id));
-                if constexpr (kBits) {
-                    if (cull) cells = reached_cells<TW, TH, PPT>(r, a.rp, tx * TW, ty * TH);
-                }
+                if constexpr (kBits) cells = reached_cells<TW, TH, PPT>(r, a.rp, tx * TW, ty * TH);
             }
-            if (kBits && cull) {
+            if constexpr (kBits) {
                 const int word = k0 / 64 + wave;
 #pragma unroll
                 for (int w = 0; w < C::NW; ++w) {
@@ -225,7 +222,7 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
                 for (int j = 0; j < kVals; ++j) atomicAdd(acc + j, v[j]);
             }
         };
-        if (kBits && cull) {
+        if constexpr (kBits) {
             // only the records whose ellipse reaches this wavefront's cell, back to front
             for (int c = (cnt - 1) / 64; c >= 0; --c) {
                 const uint64_t word = s_bits[wave * kWords + c];

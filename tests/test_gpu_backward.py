@@ -218,3 +218,24 @@ def test_backward_in_two_phases(ctx):
     ctx.release(state)
     for k in NAMES:
         assert same_up_to_atomic_order(got[k], ref[k]), k
+
+
+@pytest.mark.parametrize("tile,batch,ppt", [((16, 16), 128, 2), ((32, 32), 256, 4), ((16, 16), 64, 4), ((8, 8), 64, 1)])
+@pytest.mark.parametrize("temporal", [0, 1])
+def test_unculled_lists_give_the_same_gradients(ctx, tile, batch, ppt, temporal):
+    """With tile (and opacity) culling off, the records that cannot reach
+    alpha_min in a cell are passed over while staging: image and gradients are
+    those of the culled lists."""
+    from paper_2503_16422_amd.render import GaussianModel
+    model = GaussianModel.from_scene(inputs.dense_scene(6000, seed=13), "cuda:0")
+    cam = inputs.look_at_camera(0.2, 3.0, 117, 90)
+    layout = dict(tile_w=tile[0], tile_h=tile[1], batch=batch, pixels_per_thread=ppt)
+    out = []
+    for more in ({}, dict(tile_cull=0, temporal_cull=temporal)):
+        rgb, _, state = ctx.render(model, cam, 0.4, _lib.default_cfg(**layout, **more), keep_state=True)
+        out.append((rgb, ctx.backward(state, torch.ones_like(rgb), model)))
+        torch.cuda.synchronize()
+        ctx.release(state)
+    assert torch.equal(out[0][0], out[1][0])
+    for k in NAMES:
+        assert same_up_to_atomic_order(out[1][1][k], out[0][1][k]), k
