@@ -239,3 +239,37 @@ def test_unculled_lists_give_the_same_gradients(ctx, tile, batch, ppt, temporal)
     assert torch.equal(out[0][0], out[1][0])
     for k in NAMES:
         assert same_up_to_atomic_order(out[1][1][k], out[0][1][k]), k
+
+
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_released_states_are_reused_safely(ctx, side_stream):
+    """Forward, adjoint and release of views of different sizes back to back,
+    without a synchronisation between them: a state that reuses a released
+    one's buffers gives the gradients of a fresh context, on the null stream
+    (where buffers are reused), on another stream, and from one to the other."""
+    from paper_2503_16422_amd.render import Context, GaussianModel
+    models = [GaussianModel.from_scene(scene_small(n, seed=n), "cuda:0") for n in (3000, 900, 5000)]
+    cams = [inputs.look_at_camera(0.1 * k, 3.0, 64 + 32 * k, 96) for k in range(3)]
+    ref = []
+    for m, cam in zip(models, cams):
+        c = Context(0)
+        rgb, _, st = c.render(m, cam, 0.5, keep_state=True)
+        ref.append((rgb, c.backward(st, rgb, m)))
+        torch.cuda.synchronize()
+        c.close()
+    got = []
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for k in range(9):
+        m, cam = models[k % 3], cams[k % 3]
+        with torch.cuda.stream(side if side_stream and k % 2 else torch.cuda.default_stream()):
+            rgb, _, st = ctx.render(m, cam, 0.5, keep_state=True)
+            got.append((rgb, ctx.backward(st, rgb, m)))
+            st.release()
+            with pytest.raises(RuntimeError):
+                ctx.release(type(st)(ctx, type(ctx.handle)(12345), (1, 1)))
+    torch.cuda.synchronize()
+    for k, (rgb, g) in enumerate(got):
+        assert torch.equal(rgb, ref[k % 3][0])
+        for name in NAMES:
+            assert same_up_to_atomic_order(g[name], ref[k % 3][1][name]), (k, name)
