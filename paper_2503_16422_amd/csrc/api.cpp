@@ -1254,9 +1254,9 @@ fdgs_status check_grads(const fdgs_state *S, const fdgs_grads *grads, const char
 fdgs_status enqueue_backward_2d(fdgs_ctx *ctx, fdgs_state *S, const float *dL_drgb, hipStream_t stream) {
     if (stream != nullptr) S->beyond_null_stream = true;
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(ensure(S->g2d, sizeof(float) * 9 * std::max<int64_t>(S->n_max, 1)));
+    HIP_TRY(ensure(S->g2d, sizeof(float) * kG2dStride * std::max<int64_t>(S->n_max, 1)));
     StageTimer tm(ctx, FDGS_STAGE_BWD_COMPOSITE, stream);
-    HIP_TRY(launch_fill_u32(S->g2d.as<uint32_t>(), 9 * std::max<int64_t>(S->n_max, 1), 0u, stream));
+    HIP_TRY(launch_clear_g2d(S->vis_list, S->counts.as<int64_t>(), S->n_max, S->g2d.as<float>(), stream));
     // the adjoint takes the tiles longest list first: the forward's order when it
     // made one, else one made here
     const int32_t n_tiles = S->rp.tiles_x * S->rp.tiles_y;

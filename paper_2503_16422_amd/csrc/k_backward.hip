@@ -43,11 +43,12 @@ __global__ void __launch_bounds__(kBlock) preprocess_bwd_kernel(BArgs a) {
     if (g >= n) return;
     Gauss4 G;
     if (!load_gaussian(a.m, g, G)) return;
-    const float *gi = a.g2d + i * 9;
-    const double du = gi[0], dv = gi[1];
-    const double dca = gi[2], dcb = gi[3], dcc = gi[4];
-    const double dop = gi[5];
-    const double drgb[3] = {gi[6], gi[7], gi[8]};
+    const float4 *gi = reinterpret_cast<const float4 *>(a.g2d + i * kG2dStride);
+    const float4 ga = gi[0], gb = gi[1];
+    const double du = ga.x, dv = ga.y;
+    const double dca = ga.z, dcb = ga.w, dcc = gb.x;
+    const double dop = gb.y;
+    const double drgb[3] = {gb.z, gb.w, gi[2].x};
 
     // ---- forward recompute (float64) ----
     const double nl = sqrt(G.ql[0] * G.ql[0] + G.ql[1] * G.ql[1] + G.ql[2] * G.ql[2] + G.ql[3] * G.ql[3]);
