@@ -283,7 +283,7 @@ struct fdgs_ctx {
     std::vector<fdgs_state *> states;
     Buf overflow;                  // int32 device flag
     Buf mask_frames, mask_views, mask_scratch;
-    Buf mask_flags, mask_img;      // contributed-mode visibility bytes and the keyframe image
+    Buf mask_flags;                // contributed-mode visibility bytes
     Buf prune_a, prune_b, prune_c, prune_d, prune_e, prune_times;   // score / prune work
     Buf vq_scratch;                // k-means keys, values, cluster ranges, radix scratch
     int64_t *host_counts = nullptr;  // pinned
@@ -410,7 +410,6 @@ fdgs_status fdgs_destroy(fdgs_ctx *ctx) {
     release(ctx->mask_views);
     release(ctx->mask_scratch);
     release(ctx->mask_flags);
-    release(ctx->mask_img);
     release(ctx->probe_sink);
     for (Buf *b : {&ctx->prune_a, &ctx->prune_b, &ctx->prune_c, &ctx->prune_d, &ctx->prune_e, &ctx->prune_times,
                    &ctx->vq_scratch})
@@ -633,11 +632,7 @@ fdgs_status fdgs_build_active_mask(fdgs_ctx *ctx, const fdgs_model *model, const
         cfg.alpha_min = amin;
         cfg.dilation = dil;
         cfg.pixels_per_thread = 2;
-        int64_t px_max = 1;
-        for (int v = 0; v < spec->n_views; ++v)
-            px_max = std::max<int64_t>(px_max, (int64_t)spec->views[v].width * spec->views[v].height);
         HIP_TRY(ensure(ctx->mask_flags, (size_t)((n + 3) / 4) * 4 + 4));
-        HIP_TRY(ensure(ctx->mask_img, sizeof(float) * 3 * (size_t)px_max));
         HIP_TRY(launch_fill_u32(ctx->mask_flags.as<uint32_t>(), (n + 3) / 4, 0u, stream));
         const double keys[2] = {spec->key_lo, spec->key_hi};
         for (int k = 0; k < (spec->key_hi == spec->key_lo ? 1 : 2); ++k) {
@@ -651,7 +646,7 @@ fdgs_status fdgs_build_active_mask(fdgs_ctx *ctx, const fdgs_model *model, const
                 one.n_proc = n;
                 if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, nullptr, 1, nullptr, n,
                                                  spec->views[v].width, spec->views[v].height, &cfg,
-                                                 ctx->mask_img.as<float>(), nullptr, false, stream,
+                                                 nullptr, nullptr, false, stream,
                                                  ctx->mask_flags.as<uint8_t>()))
                     return st;
             }
@@ -769,6 +764,7 @@ RenderParams make_params(const fdgs_render_cfg *cfg, int32_t W, int32_t H) {
     rp.dilation = cfg->dilation;
     rp.temporal_cull = cfg->temporal_cull ? 1 : 0;
     rp.tile_cull = cfg->tile_cull ? 1 : 0;
+    rp.colour = 1;
     rp.vanilla_level = 2.0 * std::log(1.0 / (double)cfg->alpha_min) * (1.0 + 1e-4) + 1e-4;
     return rp;
 }
@@ -783,7 +779,8 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
                         float *out_rgb, float *out_T, bool need_state, hipStream_t stream, uint8_t *contrib,
                         float *weight) {
     const char *fn = "fdgs_render";
-    const RenderParams rp = make_params(cfg, W, H);
+    RenderParams rp = make_params(cfg, W, H);
+    rp.colour = !contrib && !weight;
     const int64_t tiles_per_view = (int64_t)rp.tiles_x * rp.tiles_y;
     const int64_t n_keys = tiles_per_view * V;
     if (n_keys >= (int64_t(1) << 31)) return fail(FDGS_ERR_INVALID_ARG, "%s: too many tiles x views", fn);
@@ -1432,9 +1429,6 @@ fdgs_status fdgs_spatial_score(fdgs_ctx *ctx, const fdgs_model *model, const fdg
         if (!std::isfinite(times[v])) return fail(FDGS_ERR_INVALID_ARG, "%s: view %d time not finite", fn, v);
     }
     HIP_TRY(hipSetDevice(ctx->device));
-    int64_t px_max = 1;
-    for (int v = 0; v < n_views; ++v) px_max = std::max<int64_t>(px_max, (int64_t)cams[v].width * cams[v].height);
-    HIP_TRY(ensure(ctx->mask_img, sizeof(float) * 3 * (size_t)px_max));
     for (int v = 0; v < n_views; ++v) {
         ViewDesc one;
         one.m = kmodel(model);
@@ -1444,7 +1438,7 @@ fdgs_status fdgs_spatial_score(fdgs_ctx *ctx, const fdgs_model *model, const fdg
         one.p_off = 0;
         one.n_proc = model->n;
         if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, nullptr, 1, nullptr, model->n, cams[v].width,
-                                         cams[v].height, &c, ctx->mask_img.as<float>(), nullptr, false, stream,
+                                         cams[v].height, &c, nullptr, nullptr, false, stream,
                                          nullptr, inout_score))
             return st;
     }

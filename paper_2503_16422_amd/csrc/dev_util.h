@@ -41,17 +41,15 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
-// Sum over the 64 lanes with DPP row operations (no LDS traffic); the total
-// is valid in lane 63.  Steps: xor-1 and xor-2 inside quads, half-row mirror,
-// row mirror (every lane now holds its 16-lane row sum), then row broadcasts
-// 15 and 31 fold rows 0..3 into row 3.
+// Sums with DPP row operations (no LDS traffic).  Steps: xor-1 and xor-2 inside
+// quads, half-row mirror, row mirror (every lane then holds its 16-lane row
+// sum); the row broadcast 15 folds rows 0 and 2 into rows 1 and 3.
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ float dpp_add_c(float v) {
     const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, true);
     return v + __builtin_bit_cast(float, o);
 }
-// Sum over each row of 16 lanes, valid in every lane of the row: the first
-// four steps of the wavefront sum.
+// Sum over each row of 16 lanes, valid in every lane of the row.
 __device__ __forceinline__ float row_sum16(float v) {
     v = dpp_add_c<0xB1>(v);          // quad_perm(1,0,3,2)
     v = dpp_add_c<0x4E>(v);          // quad_perm(2,3,0,1)
@@ -59,14 +57,17 @@ __device__ __forceinline__ float row_sum16(float v) {
     v = dpp_add_c<0x140>(v);         // row_mirror
     return v;
 }
-__device__ __forceinline__ float wave_sum_to_last(float v) {
-    v = dpp_add_c<0xB1>(v);          // quad_perm(1,0,3,2)
-    v = dpp_add_c<0x4E>(v);          // quad_perm(2,3,0,1)
-    v = dpp_add_c<0x141>(v);         // row_half_mirror
-    v = dpp_add_c<0x140>(v);         // row_mirror
+// Sum over each half of the wavefront (32 lanes), valid in lanes 31 and 63.
+__device__ __forceinline__ float half_sum32(float v) {
+    v = row_sum16(v);
     v = dpp_add_c<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
-    v = dpp_add_c<0x143, 0xc>(v);    // row_bcast:31 into rows 2 and 3
     return v;
+}
+// a over the first half of the wavefront's lanes, b over the second: lane l
+// (l + 32) of the result is a (b) at l plus at l + 32.
+__device__ __forceinline__ float fold_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Exclusive sum over a block of NT threads (NT a multiple of 64, <= 1024).

@@ -6,8 +6,11 @@
 // centre, colour), then every pixel evaluates the batch.  A pixel
 // stops before the Gaussian that would take its transmittance below t_min;
 // the workgroup leaves the list as soon as every pixel has stopped.  No MFMA:
-// per (pixel, Gaussian) pair the work is an exponential and a dozen FMAs, not
-// a contraction.
+// per (pixel, Gaussian) pair the work is an exponential and a dozen vector
+// instructions, of which the three colour sums alone form a contraction (an
+// outer product of 64 weights with a record's colour).  As a 16 x (4x4x1)
+// matrix instruction in their place they gave the same bits but took longer
+// (headline frame 90 -> 99 us).
 //
 // Precision: the centre is stored as a float pair (hi + lo) and re-centred on
 // the centre of the tile's 32x32 block while staging, and the exponent is
@@ -67,6 +70,13 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
     constexpr bool kBranchy = PPT == 1 && !kBits;
     constexpr int kWords = BATCH / 64;
     __shared__ uint64_t s_bits[kBits ? C::NW * kWords : 1];
+    // kMark, kWeight: what the tile's wavefronts found for the batch's records
+    // (a flag, the sum of weights); it leaves for global memory once per record
+    // and tile.  (One access per wavefront and record, and the colours these
+    // modes do not need, made the visibility compositor 108 us a view where it
+    // takes 82 now, the score's 150 us where it takes 103.)
+    constexpr bool SIDE = MODE == kMark || MODE == kWeight;
+    __shared__ float s_side[SIDE ? BATCH : 1];
     const int n_tiles = a.rp.tiles_x * a.rp.tiles_y;
     const int view = item / n_tiles;
     const int tile = item - view * n_tiles;
@@ -86,6 +96,7 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
     constexpr bool LAST = MODE == kState || MODE == kCount;
     constexpr bool MARK = MODE == kMark;
     constexpr bool WEIGHT = MODE == kWeight;
+    constexpr bool COLOUR = !MARK && !WEIGHT;   // those modes make no image
     constexpr float kInf = __builtin_huge_valf();
     // thr[p]: the transmittance a blend must keep; t_min while the pixel is
     // live, +inf once it has stopped (or lies outside the image), so a stopped
@@ -107,6 +118,22 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
         thr[p] = inside ? tmin : kInf;
         all_done = all_done && !inside;
     }
+    // takes the records' results of a batch of cnt out; the thread that does so also stages the slot again
+    auto flush = [&](int cnt) {
+        if constexpr (SIDE) {
+            for (int k = (int)threadIdx.x; k < cnt; k += NT) {
+                const float v = s_side[k];
+                if (v == 0.0f) continue;
+                s_side[k] = 0.0f;
+                const uint32_t id = __float_as_uint(s_rec[3 * k + 2].y);
+                if constexpr (MARK) a.contrib[id] = 1;
+                else atomicAdd(&a.weight[id], v);
+            }
+        }
+    };
+    if constexpr (SIDE)
+        for (int k = (int)threadIdx.x; k < BATCH; k += NT) s_side[k] = 0.0f;
+    int held = 0;   // records of the batch before
     for (uint32_t base = start; base < end; base += BATCH) {
         if constexpr (!kBranchy) {
             bool left = false;
@@ -115,7 +142,9 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
             all_done = !left;
         }
         if (__syncthreads_count(!all_done) == 0) break;
+        flush(held);
         const int cnt = (int)min((uint32_t)BATCH, end - base);
+        held = cnt;
         // staging: thread t stages records t, t + NT, ... of the batch; with several
         // cells per tile, each wavefront also records, per target wavefront, which
         // of its 64 records reach that wavefront's cell (one ballot per cell)
@@ -160,18 +189,16 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                         break;
                     }
                     const float w = T[0] - test;   // the blend weight, as in the multi-pixel walk
-                    C0[0] = fmaf(h.z, w, C0[0]);
-                    C1[0] = fmaf(h.w, w, C1[0]);
-                    C2[0] = fmaf(s_rec[3 * k + 2].x, w, C2[0]);
+                    if constexpr (COLOUR) {
+                        C0[0] = fmaf(h.z, w, C0[0]);
+                        C1[0] = fmaf(h.w, w, C1[0]);
+                        C2[0] = fmaf(s_rec[3 * k + 2].x, w, C2[0]);
+                    }
                     T[0] = test;
                     if constexpr (LAST) last[0] = pos;
                     if constexpr (COUNT) ++blends[0];
-                    if constexpr (MARK) {
-                        // lanes here blended record k: the lowest one flags it
-                        if (lane_id() == __builtin_ctzll(__ballot(1)))
-                            a.contrib[__float_as_uint(s_rec[3 * k + 2].y)] = 1;
-                    }
-                    if constexpr (WEIGHT) atomicAdd(&a.weight[__float_as_uint(s_rec[3 * k + 2].y)], w);
+                    if constexpr (MARK) s_side[k] = 1.0f;   // the lanes here blended record k
+                    if constexpr (WEIGHT) atomicAdd(&s_side[k], w);
                 }
             }
         } else if (__ballot(!all_done) != 0ull) {
@@ -211,9 +238,11 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                     const bool ok = hit && test >= thr[p];
                     const float Tn = ok ? test : T[p];
                     const float w = T[p] - Tn;
-                    C0[p] = fmaf(h.z, w, C0[p]);
-                    C1[p] = fmaf(h.w, w, C1[p]);
-                    C2[p] = fmaf(cb, w, C2[p]);
+                    if constexpr (COLOUR) {
+                        C0[p] = fmaf(h.z, w, C0[p]);
+                        C1[p] = fmaf(h.w, w, C1[p]);
+                        C2[p] = fmaf(cb, w, C2[p]);
+                    }
                     if constexpr (LAST) last[p] = ok ? pos : last[p];
                     if constexpr (COUNT) {
                         stop[p] += (counted && thr[p] < kInf) ? 1u : 0u;
@@ -224,15 +253,10 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                     if constexpr (MARK) blended = blended || ok;
                     if constexpr (WEIGHT) wsum += w;
                 }
-                if constexpr (WEIGHT) {
-                    // one wave sum, one atomic per record and wavefront
-                    const float tot = wave_sum_to_last(wsum);
-                    if (lane == 63 && tot != 0.0f) atomicAdd(&a.weight[__float_as_uint(s_rec[3 * k + 2].y)], tot);
-                }
                 if constexpr (MARK) {
-                    const uint64_t m = __ballot(blended);
-                    if (m != 0ull && lane == __builtin_ctzll(m)) a.contrib[__float_as_uint(s_rec[3 * k + 2].y)] = 1;
+                    if (__ballot(blended) != 0ull) s_side[k] = 1.0f;   // every lane the same word
                 }
+                return wsum;
             };
             // two records per step: both alphas first (they do not depend on the
             // transmittance), so the second record's LDS reads and exponentials
@@ -242,8 +266,12 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                 float a1[PPT], a2[PPT];
                 alphas(k1, a1, amax_bits);
                 alphas(k2, a2, two ? amax_bits : 0u);
-                apply(k1, a1, true);
-                apply(k2, a2, two);
+                const float w1 = apply(k1, a1, true), w2 = apply(k2, a2, two);
+                if constexpr (WEIGHT) {
+                    // both records' sums in one register (the wavefront's halves), then over each half
+                    const float w = half_sum32(fold_halves(w1, w2));
+                    if ((lane & 31) == 31 && w != 0.0f) atomicAdd(&s_side[lane < 32 ? k1 : k2], w);
+                }
             };
             // whether some pixel of the wavefront is still live
             auto live = [&]() {
@@ -288,6 +316,10 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
             }
         }
     }
+    if constexpr (SIDE) {
+        __syncthreads();
+        flush(held);
+    }
     const int64_t plane = (int64_t)a.W * a.H;
     float *out_rgb = a.out_rgb + (int64_t)view * 3 * plane;
     uint32_t evaluated = 0, blended = 0;
@@ -296,9 +328,11 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
         const int py = py0 + p;
         if (px < a.W && py < a.H) {
             const int64_t pix = (int64_t)py * a.W + px;
-            out_rgb[pix] = C0[p] + T[p] * a.rp.bg[0];
-            out_rgb[plane + pix] = C1[p] + T[p] * a.rp.bg[1];
-            out_rgb[2 * plane + pix] = C2[p] + T[p] * a.rp.bg[2];
+            if constexpr (COLOUR) {
+                out_rgb[pix] = C0[p] + T[p] * a.rp.bg[0];
+                out_rgb[plane + pix] = C1[p] + T[p] * a.rp.bg[1];
+                out_rgb[2 * plane + pix] = C2[p] + T[p] * a.rp.bg[2];
+            }
             if (a.out_T) a.out_T[view * plane + pix] = T[p];
             if constexpr (LAST) {
                 if (a.n_contrib) a.n_contrib[view * plane + pix] = last[p];
@@ -331,7 +365,7 @@ template <int TW, int TH, int BATCH, int PPT, int MODE, bool ORDERED>
 __global__ void __launch_bounds__(TW *TH / PPT) __attribute__((amdgpu_waves_per_eu(PPT == 4 ? 1 : 8)))
 composite_kernel(CompArgs a) {
     // per staged record three float4 at one address: gx, s, c0, kx |
-    // log2 opacity, q, r, g | b, id, -, - (the exponent's staged form)
+    // log2 opacity, q, r, g | b, id, -, - (the exponent's staged form; r, g, b adjoin)
     __shared__ float4 s_rec[3 * BATCH];
     const int item = ORDERED ? (int)a.order[blockIdx.x] : (int)blockIdx.x;
     composite_item<TW, TH, BATCH, PPT, MODE>(a, item, s_rec);

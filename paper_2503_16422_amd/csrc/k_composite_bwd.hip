@@ -63,13 +63,7 @@ __device__ __forceinline__ float dpp_of(float v) {
 }
 constexpr int kVals = 9;   // sums of d, d dx, d v, d dx^2, d dx dy, d dy^2; colour r, g, b
 
-// a over the first half of the wavefront's lanes, b over the second: lane l
-// (l + 32) of the result is a (b) at l plus at l + 32.
-__device__ __forceinline__ float fold32(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// The same over each pair of rows of 16 lanes: a in the even rows, b in the odd ones.
+// fold_halves over each pair of rows of 16 lanes: a in the even rows, b in the odd ones.
 __device__ __forceinline__ float fold16(float a, float b) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -82,7 +76,7 @@ __device__ __forceinline__ float fold16(float a, float b) {
 __device__ __forceinline__ float wave_sums18(const float (&v1)[kVals], const float (&v2)[kVals], int lane) {
     float x[kVals];
 #pragma unroll
-    for (int j = 0; j < kVals; ++j) x[j] = fold32(v1[j], v2[j]);          // record = lane / 32
+    for (int j = 0; j < kVals; ++j) x[j] = fold_halves(v1[j], v2[j]);          // record = lane / 32
     float y[5];
 #pragma unroll
     for (int j = 0; j < 4; ++j) y[j] = fold16(x[2 * j], x[2 * j + 1]);    // value's bit 0 = lane / 16 % 2

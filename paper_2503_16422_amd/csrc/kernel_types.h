@@ -44,6 +44,7 @@ struct RenderParams {
     float alpha_min, alpha_max, t_min, dilation;
     int32_t temporal_cull;
     int32_t tile_cull;      // list a record only in the tiles its ellipse reaches
+    int32_t colour;         // 0: no image is made (visibility, score passes): records without colour
     double vanilla_level;   // cut level without opacity culling, incl. margin
 };
 
