@@ -73,6 +73,13 @@ __device__ __forceinline__ float clamp_alpha(float v, uint32_t amax_bits) {
 // Transmittance after blending alpha in front of T.
 __device__ __forceinline__ float after(float T, float alpha) { return fmaf(-alpha, T, T); }
 
+// a over the first half of the wavefront's lanes, b over the second: lane l
+// (l + 32) of the result is a (b) at l plus at l + 32.
+__device__ __forceinline__ float fold_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Thread layout of both compositors: each wavefront owns a CW x CH block
 // ("cell") of the tile and each of its threads PPT consecutive pixels of one
 // column of the cell (TW x TH / PPT threads); the column's dx terms and the

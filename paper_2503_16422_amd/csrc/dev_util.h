@@ -63,13 +63,6 @@ __device__ __forceinline__ float half_sum32(float v) {
     v = dpp_add_c<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
     return v;
 }
-// a over the first half of the wavefront's lanes, b over the second: lane l
-// (l + 32) of the result is a (b) at l plus at l + 32.
-__device__ __forceinline__ float fold_halves(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // Exclusive sum over a block of NT threads (NT a multiple of 64, <= 1024).
 // `tmp` must hold NT/64 + 1 elements of shared memory.  Returns the thread's
 // exclusive prefix; *total receives the block total.  Contains barriers.
