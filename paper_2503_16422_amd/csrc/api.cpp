@@ -145,7 +145,16 @@ void release(Buf &b) {
 }
 
 constexpr int32_t kDefaultPpt = 2;
-constexpr int64_t kBucketMaxN = int64_t(1) << 20;   // largest processed count ordered by buckets
+constexpr int64_t kBucketMaxN = int64_t(1) << 20;   // largest processed count of a view ordered by buckets
+
+// Several views of one forward pass: device copies of their descriptions and of
+// the view of each chunk of entries, and the largest processed count.
+struct ViewTable {
+    const ViewDesc *views = nullptr;
+    const uint32_t *chunk_view = nullptr;
+    int32_t V = 1;
+    int64_t max_n = 0;
+};
 
 bool valid_tile(int w, int h) {
     return (w == 8 && h == 8) || (w == 16 && h == 16) || (w == 32 && (h == 8 || h == 16 || h == 32));
@@ -165,9 +174,9 @@ struct fdgs_state {
     bool has_g2d = false;   // a backward's first phase ran since the last forward
     bool ordered = false;   // sched holds the last forward's tiles longest list first
     // per processed Gaussian
-    Buf rec, depth_key, rect, tiles, visible, vis_pos, order_k, order_v, order_k2, order_v2, offsets, view_of;
-    Buf bucket;        // depth buckets: counts, cursors, starts, key range
-    Buf vis_count;     // visible entries per preprocess workgroup
+    Buf rec, depth_key, rect, tiles, visible, vis_pos, order_k, order_v, order_k2, order_v2, offsets;
+    Buf bucket;        // depth buckets (BucketWork)
+    Buf vis_count;     // per preprocess workgroup: visible entries, then their key ranges
     // per instance
     Buf tkeys, tids, tkeys2, tids2;
     // per tile / pixel
@@ -199,7 +208,7 @@ struct fdgs_state {
     template <typename F>
     void each(F f) {
         for (Buf *b : {&rec, &depth_key, &rect, &tiles, &visible, &vis_pos, &order_k, &order_v, &order_k2,
-                       &order_v2, &offsets, &view_of, &bucket, &vis_count, &tkeys, &tids, &tkeys2, &tids2, &ranges, &sched,
+                       &order_v2, &offsets, &bucket, &vis_count, &tkeys, &tids, &tkeys2, &tids2, &ranges, &sched,
                        &T_final, &n_contrib, &counts, &g2d, &scratch})
             f(*b);
     }
@@ -518,7 +527,7 @@ fdgs_state *find_state(fdgs_ctx *ctx, fdgs_state *s) {
     return nullptr;
 }
 
-fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const ViewDesc *table, int32_t V,
+fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const ViewTable &vt,
                         const int64_t *n_dev, int64_t n_total, int32_t W, int32_t H, const fdgs_render_cfg *cfg,
                         float *out_rgb, float *out_T, bool need_state, hipStream_t stream,
                         uint8_t *contrib = nullptr, float *weight = nullptr);
@@ -644,7 +653,7 @@ fdgs_status fdgs_build_active_mask(fdgs_ctx *ctx, const fdgs_model *model, const
                 one.idx = nullptr;
                 one.p_off = 0;
                 one.n_proc = n;
-                if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, nullptr, 1, nullptr, n,
+                if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, ViewTable(), nullptr, n,
                                                  spec->views[v].width, spec->views[v].height, &cfg,
                                                  nullptr, nullptr, false, stream,
                                                  ctx->mask_flags.as<uint8_t>()))
@@ -770,15 +779,16 @@ RenderParams make_params(const fdgs_render_cfg *cfg, int32_t W, int32_t H) {
 }
 
 // The forward pipeline for V views of one resolution.  V == 1: `one` by value,
-// processed count optionally on the device (n_dev).  V > 1: `table` is a
-// device copy of the views with host-known counts summing to n_total.
+// processed count optionally on the device (n_dev).  Otherwise `vt` holds the
+// views, with host-known counts, and n_total covers their padded chunks.
 // With capture set nothing may synchronise or allocate: the caller guarantees
 // buffers are already large enough and a fixed instance capacity is given.
-fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const ViewDesc *table, int32_t V,
+fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const ViewTable &vt,
                         const int64_t *n_dev, int64_t n_total, int32_t W, int32_t H, const fdgs_render_cfg *cfg,
                         float *out_rgb, float *out_T, bool need_state, hipStream_t stream, uint8_t *contrib,
                         float *weight) {
     const char *fn = "fdgs_render";
+    const int32_t V = vt.V;
     RenderParams rp = make_params(cfg, W, H);
     rp.colour = !contrib && !weight;
     const int64_t tiles_per_view = (int64_t)rp.tiles_x * rp.tiles_y;
@@ -798,12 +808,14 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     HIP_TRY(ensure(S->order_k2, sizeof(uint32_t) * n_max));
     HIP_TRY(ensure(S->order_v2, sizeof(uint32_t) * n_max));
     HIP_TRY(ensure(S->offsets, sizeof(uint64_t) * n_max));
-    if (V > 1) HIP_TRY(ensure(S->view_of, sizeof(uint32_t) * n_max));
-    // one view of at most kBucketMaxN processed Gaussians: depth order by buckets (three launches)
-    const bool by_buckets = V == 1 && n_max <= kBucketMaxN;
-    const int64_t n_buckets = int64_t(1) << bucket_log2_for(n_max);
-    if (by_buckets) HIP_TRY(ensure(S->bucket, sizeof(uint32_t) * bucket_scratch_words(n_max)));
-    uint32_t *bwork = by_buckets ? S->bucket.as<uint32_t>() : nullptr;
+    // views of at most kBucketMaxN processed Gaussians: depth order and offsets by buckets (three launches)
+    const int64_t n_view_max = vt.views ? vt.max_n : n_max;
+    const bool by_buckets = n_max > 0 && n_view_max <= kBucketMaxN;
+    size_t bucket_words = 0, bucket_clear = 0;
+    if (by_buckets) {
+        (void)bucket_work(nullptr, n_view_max, V, &bucket_words, &bucket_clear);
+        HIP_TRY(ensure(S->bucket, sizeof(uint32_t) * bucket_words));
+    }
     HIP_TRY(ensure(S->counts, sizeof(int64_t) * 4));
     HIP_TRY(ensure(S->ranges, sizeof(uint32_t) * 2 * n_keys));
     if (cfg->schedule) HIP_TRY(ensure(S->sched, sizeof(uint32_t) * n_keys));
@@ -814,54 +826,56 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     const size_t scratch = std::max(scan_scratch_bytes(n_max), sort_scratch_bytes(n_max));
     HIP_TRY(ensure(S->scratch, scratch));
     int64_t *counts = S->counts.as<int64_t>();
-    uint32_t *view_of = V > 1 ? S->view_of.as<uint32_t>() : nullptr;
 
-    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * (size_t)((n_total + kPreprocessBlock - 1) / kPreprocessBlock)));
-    PreprocOut po{S->rec.as<Rec2D>(), S->depth_key.as<uint64_t>(), S->rect.as<int32_t>(),
-                  S->tiles.as<uint32_t>(), S->visible.as<uint8_t>(), view_of, S->vis_count.as<uint32_t>()};
+    const int64_t pre_blocks = (n_total + kPreprocessBlock - 1) / kPreprocessBlock;
+    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * 3 * (size_t)pre_blocks));
+    uint32_t *vis_count = S->vis_count.as<uint32_t>(), *block_range = vis_count + pre_blocks;
+    PreprocOut po{S->rec.as<Rec2D>(), S->depth_key.as<uint64_t>(), S->rect.as<int32_t>(), S->tiles.as<uint32_t>(),
+                  S->visible.as<uint8_t>(), vis_count, block_range, S->bucket.as<uint32_t>(),
+                  by_buckets ? (int64_t)bucket_clear : 0};
     {
         StageTimer tm(ctx, FDGS_STAGE_PREPROCESS, stream);
-        HIP_TRY(launch_preprocess(one, table, V, n_dev, n_total, rp, po, stream));
+        HIP_TRY(launch_preprocess(one, vt.views, vt.chunk_view, V, n_dev, n_total, rp, po, stream));
     }
-    {
+    // the compacted list of visible entries: the radix sort's input, and the adjoint's
+    if (!by_buckets || need_state) {
         StageTimer tm(ctx, FDGS_STAGE_COMPACT, stream);
         if (need_state) HIP_TRY(ensure(S->vis_pos, sizeof(uint32_t) * n_max));
         HIP_TRY(compact_visible(S->visible.as<uint8_t>(), S->depth_key.as<uint64_t>(), n_dev, n_max, counts + 0,
                                 S->order_k.as<uint32_t>(), S->order_v.as<uint32_t>(),
-                                need_state ? S->vis_pos.as<uint32_t>() : nullptr, bwork, by_buckets ? 2 * n_buckets : 0,
-                                by_buckets ? bwork + 3 * n_buckets + 1 : nullptr, S->scratch.p, stream,
-                                S->vis_count.as<uint32_t>()));
+                                need_state ? S->vis_pos.as<uint32_t>() : nullptr, nullptr, 0, nullptr, S->scratch.p,
+                                stream, vis_count));
     }
     uint32_t *ov = nullptr;
-    {
+    if (by_buckets) {
         StageTimer tm(ctx, FDGS_STAGE_DEPTH_SORT, stream);
-        if (by_buckets) {
-            ov = S->order_v2.as<uint32_t>();
-            HIP_TRY(depth_order_buckets(S->order_k.as<uint32_t>(), S->order_v.as<uint32_t>(), counts + 0, n_max,
-                                        S->depth_key.as<uint64_t>(), bwork, S->order_v.as<uint32_t>(),
-                                        S->order_k2.as<uint32_t>(), ov, stream));
-        } else {
-            int alt = 0;
-            HIP_TRY(radix_sort_u32(S->order_k.as<uint32_t>(), S->order_v.as<uint32_t>(), S->order_k2.as<uint32_t>(),
-                                   S->order_v2.as<uint32_t>(), counts + 0, n_max, 0, 32, S->scratch.p, &alt, stream));
-            uint32_t *ok = alt ? S->order_k2.as<uint32_t>() : S->order_k.as<uint32_t>();
-            ov = alt ? S->order_v2.as<uint32_t>() : S->order_v.as<uint32_t>();
-            HIP_TRY(launch_fix_depth_ties(ok, ov, S->depth_key.as<uint64_t>(), counts + 0, n_max,
-                                          ctx->overflow.as<int32_t>(), stream));
-            if (V > 1) {
-                // group by view, keeping the depth order inside each view (stable)
-                uint32_t *kv = alt ? S->order_k.as<uint32_t>() : S->order_k2.as<uint32_t>();
-                uint32_t *vv = alt ? S->order_v.as<uint32_t>() : S->order_v2.as<uint32_t>();
-                HIP_TRY(launch_gather_u32(view_of, ov, ok, counts + 0, n_max, stream));
-                int alt_v = 0;
-                HIP_TRY(radix_sort_u32(ok, ov, kv, vv, counts + 0, n_max, 0, std::max(1, bits_for(V)), S->scratch.p,
-                                       &alt_v, stream));
-                if (alt_v) ov = vv;
-            }
+        ov = S->order_v2.as<uint32_t>();
+        HIP_TRY(depth_order_views(S->visible.as<uint8_t>(), S->depth_key.as<uint64_t>(), S->tiles.as<uint32_t>(),
+                                  block_range, n_dev, n_max, vt.views, vt.chunk_view, V, n_view_max,
+                                  S->bucket.as<uint32_t>(), S->order_v.as<uint32_t>(), S->order_k2.as<uint32_t>(), ov,
+                                  S->offsets.as<uint64_t>(), counts, stream));
+    } else {
+        StageTimer tm(ctx, FDGS_STAGE_DEPTH_SORT, stream);
+        int alt = 0;
+        HIP_TRY(radix_sort_u32(S->order_k.as<uint32_t>(), S->order_v.as<uint32_t>(), S->order_k2.as<uint32_t>(),
+                               S->order_v2.as<uint32_t>(), counts + 0, n_max, 0, 32, S->scratch.p, &alt, stream));
+        uint32_t *ok = alt ? S->order_k2.as<uint32_t>() : S->order_k.as<uint32_t>();
+        ov = alt ? S->order_v2.as<uint32_t>() : S->order_v.as<uint32_t>();
+        HIP_TRY(launch_fix_depth_ties(ok, ov, S->depth_key.as<uint64_t>(), counts + 0, n_max,
+                                      ctx->overflow.as<int32_t>(), stream));
+        if (V > 1) {
+            // group by view, keeping the depth order inside each view (stable)
+            uint32_t *kv = alt ? S->order_k.as<uint32_t>() : S->order_k2.as<uint32_t>();
+            uint32_t *vv = alt ? S->order_v.as<uint32_t>() : S->order_v2.as<uint32_t>();
+            HIP_TRY(launch_gather_view(vt.chunk_view, ov, ok, counts + 0, n_max, stream));
+            int alt_v = 0;
+            HIP_TRY(radix_sort_u32(ok, ov, kv, vv, counts + 0, n_max, 0, std::max(1, bits_for(V)), S->scratch.p,
+                                   &alt_v, stream));
+            if (alt_v) ov = vv;
         }
     }
     S->vis_list = need_state ? S->vis_pos.as<uint32_t>() : nullptr;
-    {
+    if (!by_buckets) {
         StageTimer tm(ctx, FDGS_STAGE_OFFSETS, stream);
         HIP_TRY(scan_u32_to_u64(S->tiles.as<uint32_t>(), ov, S->offsets.as<uint64_t>(), counts + 0, n_max,
                                 counts + 1, S->scratch.p, stream));
@@ -887,7 +901,7 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     HIP_TRY(ensure(S->scratch, std::max(scratch, sort_scratch_bytes(capacity, hist_cols))));
     {
         StageTimer tm(ctx, FDGS_STAGE_DUPLICATE, stream);
-        HIP_TRY(launch_duplicate(ov, S->offsets.as<uint64_t>(), S->rect.as<int32_t>(), S->rec.as<Rec2D>(), view_of, counts + 0, n_max, rp,
+        HIP_TRY(launch_duplicate(ov, S->offsets.as<uint64_t>(), S->rect.as<int32_t>(), S->rec.as<Rec2D>(), vt.chunk_view, counts + 0, n_max, rp,
                                  S->tkeys.as<uint32_t>(), S->tids.as<uint32_t>(), counts + 1, capacity,
                                  ctx->overflow.as<int32_t>(), hist_cols ? S->scratch.as<uint32_t>() : nullptr,
                                  radix_first_bits(0, tile_bits), hist_cols, stream));
@@ -977,7 +991,7 @@ fdgs_status fdgs_render_forward(fdgs_ctx *ctx, const fdgs_model *model, const ui
     one.p_off = 0;
     one.n_proc = model->n;
     const int64_t *n_dev = idx ? n_idx_dev : nullptr;
-    if (fdgs_status st = run_forward(ctx, S, &one, nullptr, 1, n_dev, model->n, cam->width, cam->height, cfg,
+    if (fdgs_status st = run_forward(ctx, S, &one, ViewTable(), n_dev, model->n, cam->width, cam->height, cfg,
                                      out_rgb, out_T, keep_state != nullptr, stream))
         return st;
     S->model = *model;
@@ -1015,6 +1029,19 @@ fdgs_status check_batch(const fdgs_model *scenes, int32_t n_scenes, const fdgs_v
     return FDGS_OK;
 }
 
+// Entries a view takes in the concatenated buffers: whole chunks, at least one.
+int64_t padded_entries(int64_t n) { return std::max<int64_t>((n + kViewChunk - 1) / kViewChunk, 1) * kViewChunk; }
+
+// What a ViewTable points to: the views, then the view of each of the n_total / kViewChunk chunks.
+std::vector<unsigned char> view_table_bytes(const std::vector<ViewDesc> &table, int64_t n_total) {
+    std::vector<unsigned char> bytes(sizeof(ViewDesc) * table.size() + sizeof(uint32_t) * (size_t)(n_total / kViewChunk));
+    std::memcpy(bytes.data(), table.data(), sizeof(ViewDesc) * table.size());
+    uint32_t *chunk = reinterpret_cast<uint32_t *>(bytes.data() + sizeof(ViewDesc) * table.size());
+    for (size_t v = 0; v < table.size(); ++v)
+        for (int64_t c = 0; c < padded_entries(table[v].n_proc) / kViewChunk; ++c) *chunk++ = (uint32_t)v;
+    return bytes;
+}
+
 // Enqueue every launch of a batch (no graph handling).
 fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_view *views, int32_t n_views,
                           const fdgs_render_cfg *cfg, int32_t per_launch, bool upload, float *out_rgb,
@@ -1029,7 +1056,7 @@ fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_vi
     for (int32_t c = 0; c < n_launch; ++c) {
         const int32_t v0 = c * per_launch, V = std::min(per_launch, n_views - v0);
         std::vector<ViewDesc> table(V);
-        int64_t off = 0;
+        int64_t off = 0, max_n = 0;
         for (int32_t k = 0; k < V; ++k) {
             const fdgs_view &w = views[v0 + k];
             ViewDesc &d = table[k];
@@ -1039,23 +1066,30 @@ fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_vi
             d.idx = w.idx;
             d.n_proc = w.idx ? w.n_idx : scenes[w.scene].n;
             d.p_off = off;
-            off += d.n_proc;
+            off += padded_entries(d.n_proc);
+            max_n = std::max(max_n, d.n_proc);
         }
         if (off >= (int64_t(1) << 32))
             return fail(FDGS_ERR_CAPACITY, "fdgs_render_batch: %lld Gaussians in one launch exceed 2^32",
                         (long long)off);
         Buf &tb = ctx->batch_tables[c];
         if (upload) {
-            HIP_TRY(ensure(tb, sizeof(ViewDesc) * V));
-            HIP_TRY(hipMemcpy(tb.p, table.data(), sizeof(ViewDesc) * V, hipMemcpyHostToDevice));
+            const std::vector<unsigned char> bytes = view_table_bytes(table, off);
+            HIP_TRY(ensure(tb, bytes.size()));
+            HIP_TRY(hipMemcpy(tb.p, bytes.data(), bytes.size(), hipMemcpyHostToDevice));
         }
         if (V == 1) {
-            if (fdgs_status st = run_forward(ctx, &ctx->batch_state, &table[0], nullptr, 1, nullptr, off, W, H, cfg,
+            if (fdgs_status st = run_forward(ctx, &ctx->batch_state, &table[0], ViewTable(), nullptr, table[0].n_proc, W, H, cfg,
                                              out_rgb + v0 * img, nullptr, false, stream))
                 return st;
         } else {
-            if (fdgs_status st = run_forward(ctx, &ctx->batch_state, nullptr, tb.as<ViewDesc>(), V, nullptr, off, W,
-                                             H, cfg, out_rgb + v0 * img, nullptr, false, stream))
+            ViewTable vt;
+            vt.views = tb.as<ViewDesc>();
+            vt.chunk_view = reinterpret_cast<const uint32_t *>(vt.views + V);
+            vt.V = V;
+            vt.max_n = max_n;
+            if (fdgs_status st = run_forward(ctx, &ctx->batch_state, nullptr, vt, nullptr, off, W, H, cfg,
+                                             out_rgb + v0 * img, nullptr, false, stream))
                 return st;
         }
     }
@@ -1437,7 +1471,7 @@ fdgs_status fdgs_spatial_score(fdgs_ctx *ctx, const fdgs_model *model, const fdg
         one.idx = nullptr;
         one.p_off = 0;
         one.n_proc = model->n;
-        if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, nullptr, 1, nullptr, model->n, cams[v].width,
+        if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, ViewTable(), nullptr, model->n, cams[v].width,
                                          cams[v].height, &c, nullptr, nullptr, false, stream,
                                          nullptr, inout_score))
             return st;

@@ -14,7 +14,11 @@ hipError_t launch_slice(const KModel &m, double t, const uint32_t *idx, int64_t 
                         float *mean3, float *cov3, float *p, hipStream_t s);
 
 // One (scene, camera, time) view of a forward pass.  Its processed entries
-// occupy [p_off, p_off + n_proc) of the concatenated per-Gaussian buffers.
+// occupy [p_off, p_off + n_proc) of the concatenated per-Gaussian buffers.  With
+// several views each starts at a whole chunk of kViewChunk entries and has at
+// least one: a workgroup's entries belong to one view, and chunk_view (one
+// word per chunk) names it.
+constexpr int kViewChunk = 4096;
 struct ViewDesc {
     KModel m;
     KCam cam;
@@ -30,15 +34,18 @@ struct PreprocOut {
     int32_t *rect;       // [P][4]
     uint32_t *tiles;     // [P] tiles touched (0 = not visible)
     uint8_t *visible;    // [P]
-    uint32_t *view_of;   // [P] view of each entry (written when V > 1)
     uint32_t *vis_count; // [ceil(P / kPreprocessBlock)] visible entries per workgroup, or NULL
+    uint32_t *block_range;   // [2 ceil(P / kPreprocessBlock)] [min, max] float32 depth bits of a workgroup's visible entries
+    uint32_t *clear;     // [n_clear] words the launch zeroes
+    int64_t n_clear;
 };
 // Entries per preprocess workgroup (its visible counts feed the compaction's scan).
 constexpr int kPreprocessBlock = 256;
 // V == 1: `one` is passed by value and n_dev may hold the device count.
-// V > 1: `table` is a device array of V views with host-known counts.
-hipError_t launch_preprocess(const ViewDesc *one, const ViewDesc *table, int32_t V, const int64_t *n_dev,
-                             int64_t n_total, const RenderParams &rp, const PreprocOut &out, hipStream_t s);
+// Otherwise `table` is a device array of V views with host-known counts and
+// n_total is a multiple of kViewChunk.
+hipError_t launch_preprocess(const ViewDesc *one, const ViewDesc *table, const uint32_t *chunk_view, int32_t V,
+                             const int64_t *n_dev, int64_t n_total, const RenderParams &rp, const PreprocOut &out, hipStream_t s);
 
 struct MaskArgs {
     const double *frames;   // device [n_frames]
@@ -81,6 +88,24 @@ size_t bucket_scratch_words(int64_t n_max);
 hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, const int64_t *n_vis_dev, int64_t n_max,
                                const uint64_t *depth_key, uint32_t *work, uint32_t *alt, uint32_t *bucketed,
                                uint32_t *out, hipStream_t s);
+// Bucket arrays of V views of at most n_view_max entries: nb = 2^bucket_log2_for(n_view_max) buckets per view.
+struct BucketWork {
+    uint64_t *count;      // per bucket: entries (above bit 43) and their tiles
+    uint64_t *view;       // the same per view
+    uint64_t *tstart;     // tiles before a bucket
+    uint32_t *start;      // entries before a bucket (one more word)
+    uint32_t *range;      // per view: lowest and highest key, and the part of them that the buckets divide
+};
+// Lays them out in `words` (null: sizes only); the first *n_clear of *n_words words have to be zero before
+// depth_order_views.
+BucketWork bucket_work(uint32_t *words, int64_t n_view_max, int32_t V, size_t *n_words, size_t *n_clear);
+// Depth order of V views' visible entries from the preprocess's output (see PreprocOut; table and chunk_view
+// null: one view of min(*n_dev, n_total) entries): out[0..n_vis) = positions by (view, depth_key[pos], pos),
+// offsets[j] = tiles of the entries before the j-th, counts[0], counts[1] = visible entries and tiles in all.
+hipError_t depth_order_views(const uint8_t *visible, const uint64_t *depth_key, const uint32_t *tiles,
+                             const uint32_t *block_range, const int64_t *n_dev, int64_t n_total, const ViewDesc *table,
+                             const uint32_t *chunk_view, int32_t V, int64_t n_view_max, uint32_t *work, uint32_t *alt,
+                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s);
 hipError_t compact_bits(const uint32_t *bits, int64_t n, uint32_t *idx, int64_t *count,
                         void *scratch, hipStream_t s);
 size_t compact_scratch_bytes(int64_t n);
@@ -103,18 +128,18 @@ hipError_t launch_scatter_visible(const uint8_t *visible, const uint32_t *pos,
 // flag |= 2 when a run of equal float32 depths is too long to reorder.
 hipError_t launch_fix_depth_ties(uint32_t *keys32, uint32_t *vals, const uint64_t *depth_key,
                                  const int64_t *n_vis_dev, int64_t n_max, int32_t *flag, hipStream_t s);
-// Tile key = view * tiles_per_view + ty * tiles_x + tx (view_of null: view 0).  Instances are written
+// Tile key = view * tiles_per_view + ty * tiles_x + tx (chunk_view null: view 0).  Instances are written
 // in windows of duplicate_window(capacity); with hist, window w also writes hist[d * hist_cols + w] = its count
 // of keys whose low hist_bits bits equal d (d < 256), and the launch has exactly hist_cols windows.
 int duplicate_window(int64_t capacity);
 hipError_t launch_duplicate(const uint32_t *order, const uint64_t *offsets, const int32_t *rect,
-                            const Rec2D *rec, const uint32_t *view_of, const int64_t *n_vis_dev, int64_t n_max,
+                            const Rec2D *rec, const uint32_t *chunk_view, const int64_t *n_vis_dev, int64_t n_max,
                             const RenderParams &rp, uint32_t *tile_keys, uint32_t *ids,
                             const int64_t *n_inst_dev, int64_t capacity, int32_t *overflow, uint32_t *hist,
                             int hist_bits, int64_t hist_cols, hipStream_t s);
-// dst[j] = src[idx[j]] for j < count.
-hipError_t launch_gather_u32(const uint32_t *src, const uint32_t *idx, uint32_t *dst, const int64_t *n_dev,
-                             int64_t n_max, hipStream_t s);
+// dst[j] = the view of entry idx[j] for j < count.
+hipError_t launch_gather_view(const uint32_t *chunk_view, const uint32_t *idx, uint32_t *dst, const int64_t *n_dev,
+                              int64_t n_max, hipStream_t s);
 hipError_t launch_tile_ranges(const uint32_t *tile_keys, const int64_t *n_inst_dev, int64_t n_max,
                               int32_t n_tiles, uint32_t *ranges, hipStream_t s);
 

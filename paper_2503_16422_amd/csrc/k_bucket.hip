@@ -1,26 +1,36 @@
-// Depth order of the visible Gaussians of one view by bucketing (Eq. 2 blends
-// "sorted by depth"; the order is (float64 depth, processing position)).
+// Depth order of the visible Gaussians by bucketing (Eq. 2 blends "sorted by
+// depth"; the order is (view, float64 depth, processing position)).
 //
 // A frame of a few hundred thousand Gaussians is far too small for a
 // multi-pass radix sort to be bound by anything but its launches (three per
-// digit pass).  Here three kernels produce the same order:
+// digit pass).  Here three kernels produce the same order, and with it the
+// exclusive sums of the tile counts that the emission needs:
 //   1. count: each visible key (float32 depth bits, a monotone image of the
-//      float64 depth) falls into one of NB buckets spread linearly over the
-//      frame's [min, max] key range (found by the compaction); per-block LDS
-//      counts, one global add per non-empty bucket.
-//   2. scatter: every block scans the NB counts itself (no separate scan
-//      launch), reserves a contiguous slot range per bucket with one global
-//      add per non-empty bucket, and writes its positions there.  The order
-//      inside a bucket depends on the scheduling and is repaired by 3.
+//      float64 depth) falls into one of NB buckets of its view, spread linearly
+//      over the range that holds nearly all keys (KeyRange); per-block LDS
+//      counts and tile sums (one 64-bit word), one global add per non-empty bucket.  The adds
+//      return the block's place in each bucket, so every entry leaves with its
+//      bucket and its slot there.  The order inside a bucket depends on the scheduling
+//      and is repaired by 3.
+//   2. scatter: every block scans its view's NB counts itself (no separate scan
+//      launch) and writes its positions to their slots.  The first block of a
+//      view publishes the buckets' starts.
 //   3. sort: one block per bucket sorts its positions by (float64 depth bits,
 //      position) -- a strict total order, so the result is unique and no tie
-//      repair is needed -- by ranking them in LDS.  A bucket larger
-//      than the LDS tile (many Gaussians at one depth) is sorted in LDS-sized
-//      chunks that the block then merges pairwise through a second buffer
-//      (each output element placed by a binary search of its co-rank).
+//      repair is needed -- by ranking them in LDS, and sums their tile counts
+//      in that order.  A bucket larger than the LDS tile (many Gaussians at one
+//      depth) is sorted in LDS-sized chunks that the block then merges pairwise
+//      through a second buffer (each output element placed by a binary search
+//      of its co-rank).
 // The bucket map is monotone in the key, so buckets in index order hold
 // increasing depths and the concatenation of the sorted buckets is the
 // sorted sequence.
+//
+// The input is either a compacted list of one view's visible entries (SrcList)
+// or what the preprocess left, culled entries included (SrcViews: one view or
+// several, each padded to whole chunks so that a block has one view).  Reading
+// flags and depths of all processed entries costs less than the two launches of
+// a compaction in front.
 #include <hip/hip_runtime.h>
 
 #include "dev_util.h"
@@ -30,126 +40,338 @@ namespace fdgs {
 namespace {
 
 constexpr int kNT = 256;
-constexpr int kKeysPerThread = 4;   // 1024 keys per counting / scattering workgroup
-constexpr int kChunk = kNT * kKeysPerThread;
-constexpr int kSortNT = 256;
-constexpr int kCap = 2048;                 // positions a block sorts in LDS at once
+// Entries per thread (KPT) of a counting / scattering workgroup: 4 up to 2^19
+// entries, so that a frame's ~140k still fill the chip, 16 above (whole view
+// chunks), where what counts is the global adds, one per workgroup and
+// non-empty bucket (16 views of 225k: count 99 -> 40 us, scatter 35 -> 27 us).
+constexpr int64_t kSmallUpTo = int64_t(1) << 19;
+static_assert(kViewChunk == 16 * kNT, "a workgroup's entries belong to one view");
+// A sorting workgroup is a chain of loads (start, position, depth) and a short
+// ranking: what counts is that all of them (one per bucket, 4096 for a frame)
+// are resident at once, 16 on a CU: 128 threads and under 10 KB of LDS.
+constexpr int kSortNT = 128;
+constexpr int kCap = 384;                  // positions a block sorts in LDS at once
 
 __device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_max) {
     return n_dev ? min(*n_dev, n_max) : n_max;
 }
 
-// Monotone map of a key in [kmin, kmax] to [0, nb).
-__device__ __forceinline__ uint32_t bucket_of(uint32_t key, uint32_t kmin, double scale, uint32_t nb) {
-    const double x = fmin((double)(key - kmin) * scale, (double)(nb - 1u));
+// A view's key range [kmin, kmax] and the part [lo, hi] of it that the buckets
+// divide; the first and the last bucket also take what lies outside.
+struct KeyRange {
+    uint32_t kmin, kmax, lo, hi;
+};
+
+// Entries [lo, hi) of the view v that chunk c holds (none: hi <= lo), and
+// whether it is the view's first chunk.
+struct Chunk {
+    int v;
+    bool first;
+    int64_t lo, hi;
+};
+
+struct SrcList {
+    const uint32_t *keys32, *vals;
+    const int64_t *n_dev;
+    int64_t n_max;
+    const uint32_t *zrange;   // [min, max] of the keys
+    __device__ __forceinline__ Chunk chunk(int64_t c, int64_t size) const {
+        return Chunk{0, c == 0, c * size, min((c + 1) * size, count_of(n_dev, n_max))};
+    }
+    __device__ __forceinline__ bool load(int64_t j, uint32_t *key) const {
+        *key = keys32[j];
+        return true;
+    }
+    __device__ __forceinline__ uint32_t pos(int64_t j) const { return vals[j]; }
+    __device__ __forceinline__ KeyRange range(const Chunk &, uint64_t *) const {
+        return KeyRange{zrange[0], zrange[1], zrange[0], zrange[1]};
+    }
+};
+
+struct SrcViews {
+    const uint8_t *visible;
+    const uint64_t *depth_key;
+    const uint32_t *block_range;   // [min, max] key of each preprocess workgroup's visible entries
+    const int64_t *n_dev;          // one view (table null): device count
+    int64_t n_max;
+    const ViewDesc *table;
+    const uint32_t *chunk_view;
+    __device__ __forceinline__ Chunk chunk(int64_t c, int64_t size) const {
+        int64_t base = 0, n;
+        int v = 0;
+        if (table) {
+            v = (int)chunk_view[c * size / kViewChunk];
+            base = table[v].p_off;
+            n = table[v].n_proc;
+        } else {
+            n = count_of(n_dev, n_max);
+        }
+        return Chunk{v, c * size == base, c * size, min((c + 1) * size, base + n)};
+    }
+    __device__ __forceinline__ bool load(int64_t j, uint32_t *key) const {
+        const uint64_t d = depth_key[j];
+        *key = __float_as_uint((float)__longlong_as_double((long long)d));   // z > 0: bit order = value order
+        return visible[j] != 0;
+    }
+    __device__ __forceinline__ uint32_t pos(int64_t j) const { return (uint32_t)j; }
+    // From the preprocess workgroups' ranges (contains barriers).  A few far
+    // outliers stretch [kmin, kmax] so that most buckets stay empty and the rest
+    // crowd (masked frame of 143k: mean bucket of an entry 160, largest 289),
+    // and ranking a bucket costs its square.  The divided part is the mean
+    // workgroup's range, which covers all but a percent, widened by 0.35 of its
+    // width on both sides.
+    __device__ __forceinline__ KeyRange range(const Chunk &w, uint64_t *s_red) const {
+        const int64_t base = table ? table[w.v].p_off : 0;
+        const int64_t n = table ? table[w.v].n_proc : count_of(n_dev, n_max);
+        const int64_t b0 = base / kPreprocessBlock, b1 = (base + n + kPreprocessBlock - 1) / kPreprocessBlock;
+        uint32_t lo = ~0u, hi = 0u;
+        uint64_t lo_sum = 0, hi_sum = 0, cnt = 0;
+        for (int64_t b = b0 + threadIdx.x; b < b1; b += kNT) {
+            const uint32_t l = block_range[2 * b], h = block_range[2 * b + 1];
+            if (l > h) continue;                             // nothing visible
+            lo = min(lo, l);
+            hi = max(hi, h);
+            lo_sum += l;
+            hi_sum += h;
+            ++cnt;
+        }
+        uint64_t both = (uint64_t)lo << 32 | (uint32_t)~hi;  // both halves want their minimum
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint64_t o = __shfl_xor(both, off, 64);
+            both = (uint64_t)min((uint32_t)(both >> 32), (uint32_t)(o >> 32)) << 32 | min((uint32_t)both, (uint32_t)o);
+            lo_sum += __shfl_xor(lo_sum, off, 64);
+            hi_sum += __shfl_xor(hi_sum, off, 64);
+            cnt += __shfl_xor(cnt, off, 64);
+        }
+        if (lane_id() == 0) {
+            uint64_t *r = s_red + 4 * wave_id();
+            r[0] = both;
+            r[1] = lo_sum;
+            r[2] = hi_sum;
+            r[3] = cnt;
+        }
+        __syncthreads();
+        KeyRange k{~0u, 0u, 0u, 0u};
+        lo_sum = hi_sum = cnt = 0;
+#pragma unroll
+        for (int q = 0; q < kNT / 64; ++q) {
+            k.kmin = min(k.kmin, (uint32_t)(s_red[4 * q] >> 32));
+            k.kmax = max(k.kmax, ~(uint32_t)s_red[4 * q]);
+            lo_sum += s_red[4 * q + 1];
+            hi_sum += s_red[4 * q + 2];
+            cnt += s_red[4 * q + 3];
+        }
+        const int64_t l = (int64_t)(lo_sum / max(cnt, (uint64_t)1)), h = (int64_t)(hi_sum / max(cnt, (uint64_t)1));
+        const int64_t more = (h - l) / 3 + 1;
+        k.lo = (uint32_t)max((int64_t)k.kmin, l - more);
+        k.hi = (uint32_t)min((int64_t)k.kmax, h + more);
+        return k;
+    }
+};
+
+constexpr int kRangeWords = 4 * (kNT / 64);      // 64-bit words of LDS that range() needs
+
+// Monotone map of a key to [0, nb).
+__device__ __forceinline__ uint32_t bucket_of(uint32_t key, const KeyRange &k, double scale, uint32_t nb) {
+    const double x = fmin((double)(max(key, k.lo) - k.lo) * scale, (double)(nb - 1u));
     return (uint32_t)x;
 }
 
-__device__ __forceinline__ double bucket_scale(const uint32_t *zrange, uint32_t nb) {
-    const uint32_t kmin = zrange[0], kmax = zrange[1];
-    return kmax >= kmin ? (double)nb / ((double)(kmax - kmin) + 1.0) : 0.0;
+__device__ __forceinline__ double bucket_scale(const KeyRange &k, uint32_t nb) {
+    return k.hi >= k.lo ? (double)nb / ((double)(k.hi - k.lo) + 1.0) : 0.0;
 }
 
-__global__ void __launch_bounds__(kNT) bucket_count_kernel(const uint32_t *keys32, const int64_t *n_dev,
-                                                           int64_t n_max, const uint32_t *zrange, uint32_t nb,
-                                                           uint32_t *count) {
-    extern __shared__ uint32_t s_cnt[];
-    const int64_t n = count_of(n_dev, n_max);
-    const int64_t base = (int64_t)blockIdx.x * kChunk;
-    if (base >= n) return;                                   // uniform
-    for (uint32_t b = threadIdx.x; b < nb; b += kNT) s_cnt[b] = 0;
-    const uint32_t kmin = zrange[0];
-    const double scale = bucket_scale(zrange, nb);
-    __syncthreads();
+// Monotone 32-bit image of the depth bits of bucket b's entries: the offset
+// from below the bucket's lowest key, without the lowest bits where the bucket
+// is too wide (a float32 step is 2^29 float64 steps; beyond the expected span
+// it saturates).
+struct Image {
+    uint64_t base;
+    int shift;
+    __device__ __forceinline__ uint32_t of(uint64_t depth) const {
+        const uint64_t d = depth > base ? (depth - base) >> shift : 0ull;
+        return (uint32_t)min(d, (uint64_t)0xfffffffeull);
+    }
+};
+__device__ __forceinline__ Image image_of(const KeyRange &k, uint32_t b, uint32_t nb) {
+    const double step = 1.0 / bucket_scale(k, nb);
+    const int64_t from = b == 0 ? (int64_t)k.kmin : (int64_t)k.lo + (int64_t)((double)b * step) - 2;
+    const int64_t to = b == nb - 1u ? (int64_t)k.kmax : (int64_t)k.lo + (int64_t)((double)(b + 1u) * step) + 2;
+    const uint64_t width = (uint64_t)max(to - from, (int64_t)0) + 3u;
+    Image im;
+    const double z = (double)__uint_as_float((uint32_t)max(from, (int64_t)0));
+    const uint64_t bits = (uint64_t)__double_as_longlong(z);
+    im.base = bits > (1ull << 29) ? bits - (1ull << 29) : 0ull;
+    im.shift = 0;
+    while (((width << 29) >> im.shift) >> 32) ++im.shift;
+    return im;
+}
+
+// An entry's code: bucket (12 bits) and slot (20 bits; a view has at most 2^20
+// entries, and its nearest one is not in the last bucket), or kNoEntry.
+constexpr uint32_t kNoEntry = ~0u;
+constexpr int kSlotBits = 20;
+constexpr int kMaxPer = 4096 / kNT;      // buckets per thread at the largest nb
+// A bucket's (block's, view's) word: entries above, their tiles in the low 43
+// bits (2^20 entries of at most 2^22 tiles).
+constexpr int kTileBits = 43;
+__device__ __forceinline__ uint32_t entries_of(uint64_t w) { return (uint32_t)(w >> kTileBits); }
+__device__ __forceinline__ uint64_t tiles_of(uint64_t w) { return w & ((uint64_t(1) << kTileBits) - 1); }
+__device__ __forceinline__ uint64_t add64(uint64_t *p, uint64_t v) {
+    return atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
+}
+
+template <int KPT, typename Src>
+__global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb, BucketWork w, const uint32_t *tiles,
+                                                           uint32_t *code) {
+    extern __shared__ uint64_t s_cnt[];                      // [nb]
+    __shared__ uint64_t s_red[kRangeWords];
+    __shared__ uint64_t s_tmp[kNT / 64 + 1];
+    const Chunk c = src.chunk(blockIdx.x, KPT * kNT);
+    if (c.lo >= c.hi) return;                                // uniform
+    // the entries' loads first: the range and the cleared counts come while they are on their way
+    uint32_t key[KPT], nt[KPT];
+    bool in[KPT];
 #pragma unroll
-    for (int r = 0; r < kKeysPerThread; ++r) {
-        const int64_t j = base + (int64_t)r * kNT + threadIdx.x;
-        if (j < n) atomicAdd(&s_cnt[bucket_of(keys32[j], kmin, scale, nb)], 1u);
+    for (int r = 0; r < KPT; ++r) {
+        const int64_t j = min(c.lo + (int64_t)r * kNT + threadIdx.x, c.hi - 1);
+        in[r] = src.load(j, &key[r]) && c.lo + (int64_t)r * kNT + threadIdx.x < c.hi;
+        nt[r] = tiles ? tiles[src.pos(j)] : 0u;
+    }
+    for (uint32_t b = threadIdx.x; b < nb; b += kNT) s_cnt[b] = 0;
+    const KeyRange kr = src.range(c, s_red);
+    if (c.first && threadIdx.x == 0) {                       // for the sort
+        uint32_t *r = w.range + 4 * (size_t)c.v;
+        r[0] = kr.kmin;
+        r[1] = kr.kmax;
+        r[2] = kr.lo;
+        r[3] = kr.hi;
+    }
+    const double scale = bucket_scale(kr, nb);
+    __syncthreads();
+    uint32_t bk[KPT], rank[KPT];
+    uint64_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        bk[r] = rank[r] = 0;
+        if (!in[r]) continue;
+        bk[r] = bucket_of(key[r], kr, scale, nb);
+        const uint64_t one = (uint64_t(1) << kTileBits) + nt[r];
+        rank[r] = entries_of(add64(&s_cnt[bk[r]], one));
+        mine += one;
     }
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < nb; b += kNT)
-        if (s_cnt[b]) atomicAdd(&count[b], s_cnt[b]);
+    // the block's place in buckets t, t + kNT, ...: all adds on their way before the first result is used
+    uint64_t *count = w.count + (size_t)c.v * nb;
+    uint64_t lc[kMaxPer], lb[kMaxPer];
+#pragma unroll
+    for (int k = 0; k < kMaxPer; ++k) {
+        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
+        lc[k] = b < nb ? s_cnt[b] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxPer; ++k) {
+        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
+        lb[k] = lc[k] ? add64(&count[b], lc[k]) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxPer; ++k) {
+        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
+        if (lc[k]) s_cnt[b] = entries_of(lb[k]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int64_t j = c.lo + (int64_t)r * kNT + threadIdx.x;
+        if (j < c.hi) code[j] = in[r] ? (bk[r] << kSlotBits | ((uint32_t)s_cnt[bk[r]] + rank[r])) : kNoEntry;
+    }
+    if (w.view) {                                            // uniform: the views' totals
+        uint64_t total;
+        block_exclusive_sum<kNT>(mine, s_tmp, &total);
+        if (threadIdx.x == 0 && total) add64(&w.view[c.v], total);
+    }
 }
 
-// Every block scans the bucket counts into s_start (exclusive); block 0 also
-// publishes them (start[nb] = total) for the sort.  Loads and the returning
-// cursor atomics are issued in batches before their results are used.
-constexpr int kMaxPer = 4096 / kNT;      // buckets per thread at the largest nb
-
-__global__ void __launch_bounds__(kNT) bucket_scatter_kernel(const uint32_t *keys32, const uint32_t *vals,
-                                                             const int64_t *n_dev, int64_t n_max,
-                                                             const uint32_t *zrange, uint32_t nb,
-                                                             const uint32_t *count, uint32_t *cursor,
-                                                             uint32_t *start, uint32_t *out) {
-    extern __shared__ uint32_t s_mem[];
-    uint32_t *s_start = s_mem;          // [nb]
-    uint32_t *s_loc = s_mem + nb;       // [nb]: block-local count, then the block's slot base
+// Every block scans its view's bucket counts into s_start (exclusive, from the
+// views before); the view's first block also publishes them (start[V nb] =
+// total) and the tile sums' scan for the sort.
+template <int KPT, typename Src>
+__global__ void __launch_bounds__(kNT) bucket_scatter_kernel(Src src, uint32_t nb, int V, BucketWork w,
+                                                             const uint32_t *code, uint32_t *out, int64_t n_out,
+                                                             bool tiles, int64_t *counts) {
+    extern __shared__ uint32_t s_start[];                    // [nb]
     __shared__ uint32_t s_tmp[kNT / 64 + 1];
-    const int64_t n = count_of(n_dev, n_max);
-    const int64_t base = (int64_t)blockIdx.x * kChunk;
-    if (base >= n && blockIdx.x != 0) return;                // uniform; block 0 always publishes
+    __shared__ uint64_t s_tmp64[kNT / 64 + 1];
+    const Chunk c = src.chunk(blockIdx.x, KPT * kNT);
+    if (c.lo >= c.hi && !c.first) return;                    // uniform; a view's first block always publishes
+    const uint64_t *count = w.count + (size_t)c.v * nb;
     // exclusive scan of the counts: thread t owns the contiguous slice [t * per, (t + 1) * per)
     const uint32_t per = nb >= (uint32_t)kNT ? nb / kNT : 1u;
     const uint32_t b0 = threadIdx.x * per;
-    uint32_t c[kMaxPer];
+    uint64_t cn[kMaxPer];
+    uint32_t cd[KPT], pos[KPT];
 #pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) c[k] = count[min(b0 + (uint32_t)k, nb - 1u)];
+    for (int k = 0; k < kMaxPer; ++k) cn[k] = count[min(b0 + (uint32_t)k, nb - 1u)];
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int64_t j = c.lo + (int64_t)r * kNT + threadIdx.x;
+        cd[r] = j < c.hi ? code[j] : kNoEntry;
+        pos[r] = j < c.hi ? src.pos(j) : 0u;
+    }
+    // entries and tiles of the views before
+    uint64_t vis_before = 0, tiles_before = 0;
+    if (c.v > 0) {                                           // uniform
+        uint64_t a = 0, t = 0;
+        for (int u = threadIdx.x; u < c.v; u += kNT) {
+            a += entries_of(w.view[u]);
+            t += tiles_of(w.view[u]);
+        }
+        block_exclusive_sum<kNT>(a, s_tmp64, &vis_before);
+        if (c.first) block_exclusive_sum<kNT>(t, s_tmp64, &tiles_before);
+    }
     uint32_t sum = 0;
 #pragma unroll
     for (int k = 0; k < kMaxPer; ++k)
-        if ((uint32_t)k < per && b0 + k < nb) sum += c[k];
+        if ((uint32_t)k < per && b0 + k < nb) sum += entries_of(cn[k]);
     uint32_t total;
-    uint32_t run = block_exclusive_sum<kNT>(sum, s_tmp, &total);
+    uint32_t run = block_exclusive_sum<kNT>(sum, s_tmp, &total) + (uint32_t)vis_before;
 #pragma unroll
     for (int k = 0; k < kMaxPer; ++k)
         if ((uint32_t)k < per && b0 + k < nb) {
             s_start[b0 + k] = run;
-            run += c[k];
+            run += entries_of(cn[k]);
         }
-    for (uint32_t b = threadIdx.x; b < nb; b += kNT) s_loc[b] = 0;
-    __syncthreads();
-    if (blockIdx.x == 0) {
-        for (uint32_t b = threadIdx.x; b < nb; b += kNT) start[b] = s_start[b];
-        if (threadIdx.x == 0) start[nb] = total;
-    }
-    if (base >= n) return;                                   // uniform (block 0 only)
-    const uint32_t kmin = zrange[0];
-    const double scale = bucket_scale(zrange, nb);
-    uint32_t bk[kKeysPerThread], rank[kKeysPerThread];
-#pragma unroll
-    for (int r = 0; r < kKeysPerThread; ++r) {
-        const int64_t j = base + (int64_t)r * kNT + threadIdx.x;
-        bk[r] = j < n ? bucket_of(keys32[j], kmin, scale, nb) : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < kKeysPerThread; ++r) {
-        const int64_t j = base + (int64_t)r * kNT + threadIdx.x;
-        rank[r] = j < n ? atomicAdd(&s_loc[bk[r]], 1u) : 0u;
-    }
-    __syncthreads();
-    // thread t reserves the slots of buckets t, t + kNT, ...
-    uint32_t lc[kMaxPer], lb[kMaxPer];
-#pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) {
-        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
-        lc[k] = b < nb ? s_loc[b] : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) {
-        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
-        lb[k] = lc[k] ? atomicAdd(&cursor[b], lc[k]) : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) {
-        const uint32_t b = threadIdx.x + (uint32_t)k * kNT;
-        if (b < nb) s_loc[b] = s_start[b] + lb[k];
-    }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kKeysPerThread; ++r) {
-        const int64_t j = base + (int64_t)r * kNT + threadIdx.x;
-        const uint32_t slot = s_loc[bk[r]] + rank[r];
-        if (j < n && slot < (uint64_t)n) out[slot] = vals[j];
+    for (int r = 0; r < KPT; ++r) {
+        if (cd[r] == kNoEntry) continue;
+        const uint32_t slot = s_start[min(cd[r] >> kSlotBits, nb - 1u)] + (cd[r] & ((1u << kSlotBits) - 1u));
+        if (slot < (uint64_t)n_out) out[slot] = pos[r];
+    }
+    if (!c.first) return;                                    // uniform
+    uint32_t *start = w.start + (size_t)c.v * nb;
+    for (uint32_t b = threadIdx.x; b < nb; b += kNT) start[b] = s_start[b];
+    const bool last = c.v == V - 1;
+    if (last && threadIdx.x == 0) start[nb] = (uint32_t)vis_before + total;
+    uint64_t all = 0;
+    if (tiles) {
+        uint64_t *tstart = w.tstart + (size_t)c.v * nb;
+        uint64_t ts = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k)
+            if ((uint32_t)k < per && b0 + k < nb) ts += tiles_of(cn[k]);
+        uint64_t trun = block_exclusive_sum<kNT>(ts, s_tmp64, &all) + tiles_before;
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k)
+            if ((uint32_t)k < per && b0 + k < nb) {
+                tstart[b0 + k] = trun;
+                trun += tiles_of(cn[k]);
+            }
+    }
+    if (last && counts && threadIdx.x == 0) {
+        counts[0] = (int64_t)(vis_before + total);
+        counts[1] = (int64_t)(tiles_before + all);
     }
 }
 
@@ -159,17 +381,40 @@ __device__ __forceinline__ bool before(uint64_t da, uint32_t pa, uint64_t db, ui
 }
 
 // One block sorts m <= kCap (key, position) pairs held in LDS by rank:
-// element e goes to the number of elements that precede it.  The order is
-// strict, so the ranks are a permutation.  Every thread compares its own
-// elements (e = t + kSortNT r) against all m, eight at a time from LDS
-// broadcasts: m^2 / kSortNT compares per thread and two barriers, which for
-// buckets of tens to a few hundred entries is far cheaper than a sorting
-// network's barrier-separated steps.  Entries [m, m rounded up to 8) are set
-// to (all ones, all ones), which precede nothing.
+// element e goes to the number of elements that precede it.  Every thread
+// compares its own elements (e = t + kSortNT r) against all m from LDS
+// broadcasts; wavefronts without elements skip the loop.  The ranks come from
+// 32-bit images of the keys first (Image): two vector instructions per compare
+// and four keys per LDS read, where the 64-bit key with the position takes
+// about six and two reads.  Two elements with one image would have one rank:
+// then s_owner[rank] misses one of them, and the order by the whole (key,
+// position), which is strict, decides.  s_owner receives each rank's element.
+// Entries [m, m rounded up to 16) of the images and to 8 of the keys are set to
+// all ones, which precede nothing.
 template <int R>
-__device__ __forceinline__ void rank_sort_r(const uint64_t *s_key, const uint32_t *s_pos, int m, uint32_t *dst) {
+__device__ __forceinline__ void ranks_by_image(const uint32_t *s_img, int m, uint32_t (&rk)[R]) {
+    uint32_t ke[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int e = (int)threadIdx.x + kSortNT * r;
+        ke[r] = e < m ? s_img[e] : 0u;
+        rk[r] = 0;
+    }
+    if ((int)(threadIdx.x & ~63u) >= m) return;           // uniform over the wavefront
+    for (int f0 = 0; f0 < m; f0 += 16) {
+        uint32_t kf[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) kf[u] = s_img[f0 + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r) rk[r] += kf[u] < ke[r] ? 1u : 0u;
+    }
+}
+template <int R>
+__device__ __forceinline__ void ranks_by_key(const uint64_t *s_key, const uint32_t *s_pos, int m, uint32_t (&rk)[R]) {
     uint64_t ke[R];
-    uint32_t pe[R], rk[R];
+    uint32_t pe[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int e = (int)threadIdx.x + kSortNT * r;
@@ -191,45 +436,107 @@ __device__ __forceinline__ void rank_sort_r(const uint64_t *s_key, const uint32_
 #pragma unroll
             for (int r = 0; r < R; ++r) rk[r] += before(kf[u], pf[u], ke[r], pe[r]) ? 1u : 0u;
     }
+}
+template <int R>
+__device__ __forceinline__ void rank_sort_r(const uint64_t *s_key, const uint32_t *s_pos, const uint32_t *s_img, int m,
+                                            uint32_t *s_owner, uint32_t *s_twice) {
+    uint32_t rk[R];
+    auto own = [&]() {
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-        if ((int)threadIdx.x + kSortNT * r < m) dst[rk[r]] = pe[r];
+        for (int r = 0; r < R; ++r)
+            if ((int)threadIdx.x + kSortNT * r < m) s_owner[rk[r]] = threadIdx.x + kSortNT * r;
+        __syncthreads();
+    };
+    ranks_by_image<R>(s_img, m, rk);
+    own();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t e = threadIdx.x + kSortNT * r;
+        if ((int)e < m && s_owner[rk[r]] != e) *s_twice = 1u;
+    }
+    __syncthreads();
+    if (*s_twice == 0u) return;                            // uniform
+    ranks_by_key<R>(s_key, s_pos, m, rk);
+    own();
 }
 
-__device__ void rank_sort(uint64_t *s_key, uint32_t *s_pos, int m, uint32_t *dst) {
+// s_owner[rank] = element for the m pairs (contains barriers, the first before any read).
+__device__ void rank_sort(uint64_t *s_key, uint32_t *s_pos, uint32_t *s_img, int m, uint32_t *s_owner,
+                          uint32_t *s_twice) {
+    for (int i = m + (int)threadIdx.x; i < ((m + 15) & ~15); i += kSortNT) s_img[i] = ~0u;
     for (int i = m + (int)threadIdx.x; i < ((m + 7) & ~7); i += kSortNT) {
         s_key[i] = ~0ull;
         s_pos[i] = ~0u;
     }
+    if (threadIdx.x == 0) *s_twice = 0u;
     __syncthreads();
-    if (m <= kSortNT) rank_sort_r<1>(s_key, s_pos, m, dst);
-    else if (m <= 2 * kSortNT) rank_sort_r<2>(s_key, s_pos, m, dst);
-    else if (m <= 4 * kSortNT) rank_sort_r<4>(s_key, s_pos, m, dst);
-    else rank_sort_r<kCap / kSortNT>(s_key, s_pos, m, dst);
+    if (m <= kSortNT) rank_sort_r<1>(s_key, s_pos, s_img, m, s_owner, s_twice);
+    else if (m <= 2 * kSortNT) rank_sort_r<2>(s_key, s_pos, s_img, m, s_owner, s_twice);
+    else rank_sort_r<kCap / kSortNT>(s_key, s_pos, s_img, m, s_owner, s_twice);
 }
 
-// Block b sorts bucket b.
-__global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *start, const uint32_t *bucketed,
-                                                              const uint64_t *depth_key, int64_t n_max,
-                                                              uint32_t *alt, uint32_t *out) {
+// Block b sorts bucket b; with tiles, offsets[j] = the tiles of the entries
+// before the j-th of the order (from the bucket's tstart).
+__global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *start, const uint32_t *range, uint32_t nb,
+                                                              const uint32_t *bucketed, const uint64_t *depth_key,
+                                                              int64_t n_max, uint32_t *alt, uint32_t *out,
+                                                              const uint32_t *tiles, const uint64_t *tstart,
+                                                              uint64_t *offsets) {
     __shared__ uint64_t s_key[kCap + 8];
-    __shared__ uint32_t s_pos[kCap + 8];
+    __shared__ __attribute__((aligned(16))) uint32_t s_img[kCap];
+    __shared__ uint32_t s_pos[kCap + 8], s_tiles[kCap], s_owner[kCap];
+    __shared__ uint32_t s_twice;
+    __shared__ uint32_t s_wave[kSortNT / 64];
+    __shared__ uint64_t s_tmp[kSortNT / 64 + 1];
     const uint32_t lo = start[blockIdx.x], hi = (uint32_t)min((int64_t)start[blockIdx.x + 1], n_max);
+    const uint32_t *r = range + 4 * (size_t)(blockIdx.x / nb);
+    const KeyRange kr{r[0], r[1], r[2], r[3]};
+    const uint64_t tiles_before = tiles ? tstart[blockIdx.x] : 0;
     const int64_t m = (int64_t)hi - lo;
     if (m <= 0) return;
+    const Image im = image_of(kr, blockIdx.x % nb, nb);
     const uint32_t last = (uint32_t)(n_max - 1);    // positions index depth_key[0, n_max)
     // sorted runs of kCap (all of the bucket when it fits)
     for (int64_t c0 = 0; c0 < m; c0 += kCap) {
         const int len = (int)min((int64_t)kCap, m - c0);
         for (int i = threadIdx.x; i < len; i += kSortNT) {
             const uint32_t pos = min(bucketed[lo + c0 + i], last);
+            const uint64_t key = depth_key[pos];
             s_pos[i] = pos;
-            s_key[i] = depth_key[pos];
+            s_key[i] = key;
+            s_img[i] = im.of(key);
+            if (tiles) s_tiles[i] = tiles[pos];
         }
-        rank_sort(s_key, s_pos, len, out + lo + c0);
+        rank_sort(s_key, s_pos, s_img, len, s_owner, &s_twice);
+        for (int j = threadIdx.x; j < len; j += kSortNT) out[lo + c0 + j] = s_pos[s_owner[j]];
+        if (m <= kCap) break;
         __syncthreads();
     }
-    if (m <= kCap) return;
+    if (m <= kCap) {
+        if (!tiles) return;
+        // exclusive sums of the tile counts in the new order: each thread's
+        // consecutive elements, the wavefront, the wavefronts before (at most
+        // kCap counts of 2^22 tiles: 32 bits hold the sums)
+        const int per = ((int)m + kSortNT - 1) / kSortNT, j0 = (int)threadIdx.x * per;
+        uint32_t t[kCap / kSortNT], sum = 0;
+#pragma unroll
+        for (int q = 0; q < kCap / kSortNT; ++q) {
+            t[q] = q < per && j0 + q < (int)m ? s_tiles[s_owner[j0 + q]] : 0u;
+            sum += t[q];
+        }
+        const uint32_t inc = wave_inclusive_sum(sum);
+        if (lane_id() == 63) s_wave[wave_id()] = inc;
+        __syncthreads();
+        uint64_t run = tiles_before + (inc - sum);
+        for (int w = 0; w < wave_id(); ++w) run += s_wave[w];
+#pragma unroll
+        for (int q = 0; q < kCap / kSortNT; ++q)
+            if (q < per && j0 + q < (int)m) {
+                offsets[lo + j0 + q] = run;
+                run += t[q];
+            }
+        return;
+    }
     // pairwise merges of runs of width w: output element i of a pair takes
     // the i-th smallest of the two runs, found by a binary search of how many
     // of them come from the first run
@@ -262,6 +569,16 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
     }
     if (src != out + lo)
         for (int64_t i = threadIdx.x; i < m; i += kSortNT) out[lo + i] = src[i];
+    if (!tiles) return;
+    uint64_t run = tiles_before;
+    for (int64_t j0 = 0; j0 < m; j0 += kSortNT) {
+        const int64_t j = j0 + threadIdx.x;
+        uint64_t total;
+        const uint64_t ex =
+            block_exclusive_sum<kSortNT>(j < m ? (uint64_t)tiles[min(src[j], last)] : uint64_t(0), s_tmp, &total);
+        if (j < m) offsets[lo + j] = run + ex;
+        run += total;
+    }
 }
 
 }  // namespace
@@ -275,24 +592,72 @@ int bucket_log2_for(int64_t n_max) {
 
 size_t bucket_scratch_words(int64_t n_max) {
     const int64_t nb = int64_t(1) << bucket_log2_for(n_max);
-    return (size_t)(3 * nb + 1 + 2);
+    return (size_t)(3 * nb + 1 + 2 + 4);
 }
+
+BucketWork bucket_work(uint32_t *words, int64_t n_view_max, int32_t V, size_t *n_words, size_t *n_clear) {
+    const size_t nb = (size_t(1) << bucket_log2_for(n_view_max)) * (size_t)V;
+    BucketWork w;
+    size_t at = 0;
+    auto take = [&](size_t n) {   // whole 64-bit words
+        uint32_t *p = words + at;
+        at += (n + 1) / 2 * 2;
+        return p;
+    };
+    w.count = reinterpret_cast<uint64_t *>(take(2 * nb));
+    w.view = reinterpret_cast<uint64_t *>(take(2 * (size_t)V));
+    *n_clear = at;
+    w.tstart = reinterpret_cast<uint64_t *>(take(2 * nb));
+    w.start = take(nb + 1);
+    w.range = take(4 * (size_t)V);
+    *n_words = at;
+    return w;
+}
+
+namespace {
+
+template <int KPT, typename Src>
+hipError_t order_buckets(const Src &src, int64_t n_view_max, int32_t V, const BucketWork &w,
+                         const uint64_t *depth_key, int64_t n_max, uint32_t *alt, uint32_t *bucketed, uint32_t *out,
+                         const uint32_t *tiles, uint64_t *offsets, int64_t *counts, hipStream_t s) {
+    const uint32_t nb = 1u << bucket_log2_for(n_view_max);
+    const int64_t chunks = (n_max + KPT * kNT - 1) / (KPT * kNT);
+    hipLaunchKernelGGL((bucket_count_kernel<KPT, Src>), dim3((unsigned)chunks), dim3(kNT),
+                       sizeof(uint64_t) * nb, s, src, nb, w, tiles, alt);
+    hipLaunchKernelGGL((bucket_scatter_kernel<KPT, Src>), dim3((unsigned)chunks), dim3(kNT), sizeof(uint32_t) * nb, s, src, nb,
+                       (int)V, w, (const uint32_t *)alt, bucketed, n_max, tiles != nullptr, counts);
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3(nb * (unsigned)V), dim3(kSortNT), 0, s, (const uint32_t *)w.start,
+                       (const uint32_t *)w.range, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles, (const uint64_t *)w.tstart,
+                       offsets);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, const int64_t *n_vis_dev, int64_t n_max,
                                const uint64_t *depth_key, uint32_t *work, uint32_t *alt, uint32_t *bucketed,
                                uint32_t *out, hipStream_t s) {
     if (n_max == 0) return hipSuccess;
     const uint32_t nb = 1u << bucket_log2_for(n_max);
-    uint32_t *count = work, *cursor = work + nb, *start = work + 2 * nb, *zrange = work + 3 * nb + 1;
-    const unsigned blocks = (unsigned)((n_max + kChunk - 1) / kChunk);
-    hipLaunchKernelGGL(bucket_count_kernel, dim3(blocks), dim3(kNT), sizeof(uint32_t) * nb, s, keys32, n_vis_dev,
-                       n_max, (const uint32_t *)zrange, nb, count);
-    hipLaunchKernelGGL(bucket_scatter_kernel, dim3(blocks), dim3(kNT), 2 * sizeof(uint32_t) * nb, s, keys32, vals,
-                       n_vis_dev, n_max, (const uint32_t *)zrange, nb, (const uint32_t *)count, cursor, start,
-                       bucketed);
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3(nb), dim3(kSortNT), 0, s, (const uint32_t *)start,
-                       (const uint32_t *)bucketed, depth_key, n_max, alt, out);
-    return hipGetLastError();
+    BucketWork w{};
+    w.count = reinterpret_cast<uint64_t *>(work);
+    w.start = work + 2 * nb;
+    w.range = work + 3 * nb + 3;
+    return order_buckets<4>(SrcList{keys32, vals, n_vis_dev, n_max, work + 3 * nb + 1}, n_max, 1, w,
+                         depth_key, n_max, alt, bucketed, out, nullptr, nullptr, nullptr, s);
+}
+
+hipError_t depth_order_views(const uint8_t *visible, const uint64_t *depth_key, const uint32_t *tiles,
+                             const uint32_t *block_range, const int64_t *n_dev, int64_t n_total, const ViewDesc *table,
+                             const uint32_t *chunk_view, int32_t V, int64_t n_view_max, uint32_t *work, uint32_t *alt,
+                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s) {
+    size_t words = 0, clear = 0;
+    const BucketWork w = bucket_work(work, n_view_max, V, &words, &clear);
+    const SrcViews src{visible, depth_key, block_range, n_dev, n_total, table, chunk_view};
+    return n_total <= kSmallUpTo ? order_buckets<4>(src, n_view_max, V, w, depth_key, n_total, alt, bucketed, out, tiles,
+                                                    offsets, counts, s)
+                                 : order_buckets<16>(src, n_view_max, V, w, depth_key, n_total, alt, bucketed, out, tiles,
+                                                     offsets, counts, s);
 }
 
 }  // namespace fdgs

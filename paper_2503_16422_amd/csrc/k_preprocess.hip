@@ -44,7 +44,8 @@ __global__ void __launch_bounds__(kBlock) slice_kernel(KModel m, double t, const
 
 struct PreArgs {
     ViewDesc one;              // the view when V == 1
-    const ViewDesc *table;     // device table when V > 1
+    const ViewDesc *table;     // device table of several views, and the view of each chunk of entries
+    const uint32_t *chunk_view;
     int32_t V;
     const int64_t *n_dev;      // device processed count (V == 1 only)
     int64_t n_total;           // processed entries over all views (upper bound when n_dev)
@@ -54,9 +55,9 @@ struct PreArgs {
 
 // Processed entry j of view vd (local position i = j - vd.p_off).  Returns
 // whether it is visible; then *rect4 and *ell describe its footprint for the
-// tile count.
+// tile count, *key its depth.
 __device__ __forceinline__ bool preprocess_one(const ViewDesc &vd, int64_t j, const PreArgs &a, int4 *rect4,
-                                               CullEllipse *ell) {
+                                               CullEllipse *ell, uint32_t *key) {
     const int64_t i = j - vd.p_off;
     const int64_t g = vd.idx ? (int64_t)vd.idx[i] : i;
     Gauss4 G;
@@ -116,9 +117,9 @@ __device__ __forceinline__ bool preprocess_one(const ViewDesc &vd, int64_t j, co
         const int4 r4 = make_int4(r.x0, r.y0, r.x1, r.y1);
         reinterpret_cast<int4 *>(a.out.rect)[j] = r4;
         *rect4 = r4;
+        *key = __float_as_uint((float)Pr.z);        // z > 0: bit order = value order
         *ell = cull_ellipse(rec, a.rp);
     }
-    a.out.visible[j] = vis ? 1 : 0;
     return vis;
 }
 
@@ -132,23 +133,41 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
     __shared__ CullEllipse s_ell[kBlock];
     __shared__ uint32_t s_rbase[kBlock], s_cnt[kBlock];
     __shared__ uint32_t s_tmp[kBlock / 64 + 1];
+    __shared__ uint32_t s_range[2 * (kBlock / 64)];
     const int t = threadIdx.x;
     const int64_t j = (int64_t)blockIdx.x * kBlock + t;
-    const int64_t P = (a.V == 1 && a.n_dev) ? min(*a.n_dev, a.n_total) : a.n_total;
+    for (int64_t i = j; i < a.out.n_clear; i += (int64_t)gridDim.x * kBlock) a.out.clear[i] = 0u;
+    const int64_t P = (!a.table && a.n_dev) ? min(*a.n_dev, a.n_total) : a.n_total;
+    if ((int64_t)blockIdx.x * kBlock >= P) {               // uniform: past the processed entries
+        if (t == 0) {
+            a.out.block_range[2 * blockIdx.x] = ~0u;
+            a.out.block_range[2 * blockIdx.x + 1] = 0u;
+            if (a.out.vis_count) a.out.vis_count[blockIdx.x] = 0u;
+        }
+        return;
+    }
     bool vis = false;
     int4 r4 = make_int4(0, 0, -1, -1);
     CullEllipse ell = {};
-    if (j < P) {
-        if (a.V == 1) {
-            vis = preprocess_one(a.one, j, a, &r4, &ell);
-        } else {
-            int lo = 0, hi = a.V - 1;         // last view whose range starts at or before j
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (a.table[mid].p_off <= j) lo = mid; else hi = mid - 1;
-            }
-            a.out.view_of[j] = (uint32_t)lo;
-            vis = preprocess_one(a.table[lo], j, a, &r4, &ell);
+    uint32_t key = 0;
+    if (!a.table) {
+        if (j < P) vis = preprocess_one(a.one, j, a, &r4, &ell, &key);
+    } else {
+        // the workgroup's entries belong to one view; the last ones of its chunks may be padding
+        const ViewDesc &vd = a.table[__builtin_amdgcn_readfirstlane((int)a.chunk_view[blockIdx.x / (kViewChunk / kBlock)])];
+        if (j - vd.p_off < vd.n_proc) vis = preprocess_one(vd, j, a, &r4, &ell, &key);
+    }
+    if (j < P) a.out.visible[j] = vis ? 1 : 0;
+    {
+        uint32_t lo = vis ? key : ~0u, hi = vis ? key : 0u;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+        }
+        if (lane_id() == 0) {
+            s_range[2 * wave_id()] = lo;
+            s_range[2 * wave_id() + 1] = hi;
         }
     }
     const int tw = a.rp.tile_w, th = a.rp.tile_h;
@@ -179,6 +198,15 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
     }
     __syncthreads();
     if (j < P) a.out.tiles[j] = s_cnt[t];
+    if (t == 0) {
+        uint32_t lo = s_range[0], hi = s_range[1];
+        for (int w = 1; w < kBlock / 64; ++w) {
+            lo = min(lo, s_range[2 * w]);
+            hi = max(hi, s_range[2 * w + 1]);
+        }
+        a.out.block_range[2 * blockIdx.x] = lo;
+        a.out.block_range[2 * blockIdx.x + 1] = hi;
+    }
     if (a.out.vis_count) {                          // uniform
         const int nv = __syncthreads_count(vis);
         if (t == 0) a.out.vis_count[blockIdx.x] = (uint32_t)nv;
@@ -236,12 +264,13 @@ hipError_t launch_slice(const KModel &m, double t, const uint32_t *idx, int64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_preprocess(const ViewDesc *one, const ViewDesc *table, int32_t V, const int64_t *n_dev,
-                             int64_t n_total, const RenderParams &rp, const PreprocOut &out, hipStream_t s) {
+hipError_t launch_preprocess(const ViewDesc *one, const ViewDesc *table, const uint32_t *chunk_view, int32_t V,
+                             const int64_t *n_dev, int64_t n_total, const RenderParams &rp, const PreprocOut &out, hipStream_t s) {
     if (n_total == 0) return hipSuccess;
     PreArgs a;
     a.one = one ? *one : ViewDesc{};
     a.table = table;
+    a.chunk_view = chunk_view;
     a.V = V;
     a.n_dev = n_dev;
     a.n_total = n_total;

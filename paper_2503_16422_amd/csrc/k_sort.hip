@@ -338,7 +338,7 @@ constexpr int64_t kDupSmallUpTo = int64_t(1) << 21;
 template <int kDupE>
 __global__ void __launch_bounds__(kDupNT) duplicate_kernel(const uint32_t *order, const uint64_t *offsets,
                                                            const int32_t *rect, const Rec2D *rec,
-                                                           const uint32_t *view_of, const int64_t *n_vis_dev,
+                                                           const uint32_t *chunk_view, const int64_t *n_vis_dev,
                                                            int64_t n_max, RenderParams rp, uint32_t *tile_keys,
                                                            uint32_t *ids, const int64_t *n_inst_dev,
                                                            int64_t capacity, int32_t *overflow, uint32_t *hist,
@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kDupNT) duplicate_kernel(const uint32_t *order
             s_ell[t] = cull_ellipse(rec[id], rp);
             s_id[t] = id;
             // tile keys of view v start at v * tiles per view
-            s_base[t] = view_of ? view_of[id] * (uint32_t)(rp.tiles_x * rp.tiles_y) : 0u;
+            s_base[t] = chunk_view ? chunk_view[id / kViewChunk] * (uint32_t)(rp.tiles_x * rp.tiles_y) : 0u;
             packed = (1u << 20) | (uint32_t)(r.w / rp.tile_h - r.y / rp.tile_h + 1);
         }
         uint32_t tot;
@@ -457,10 +457,10 @@ __global__ void __launch_bounds__(kDupNT) duplicate_kernel(const uint32_t *order
     }
 }
 
-__global__ void gather_u32_kernel(const uint32_t *src, const uint32_t *idx, uint32_t *dst,
-                                  const int64_t *n_dev, int64_t n_max) {
+__global__ void gather_view_kernel(const uint32_t *chunk_view, const uint32_t *idx, uint32_t *dst,
+                                   const int64_t *n_dev, int64_t n_max) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < count_of(n_dev, n_max)) dst[j] = src[idx[j]];
+    if (j < count_of(n_dev, n_max)) dst[j] = chunk_view[idx[j] / kViewChunk];
 }
 
 __global__ void count_diff_kernel(const uint32_t *a, const uint32_t *b, int64_t n, unsigned long long *out) {
@@ -624,7 +624,7 @@ hipError_t launch_fix_depth_ties(uint32_t *keys32, uint32_t *vals, const uint64_
 int duplicate_window(int64_t capacity) { return capacity <= kDupSmallUpTo ? 1024 : 2048; }
 
 hipError_t launch_duplicate(const uint32_t *order, const uint64_t *offsets, const int32_t *rect,
-                            const Rec2D *rec, const uint32_t *view_of, const int64_t *n_vis_dev, int64_t n_max,
+                            const Rec2D *rec, const uint32_t *chunk_view, const int64_t *n_vis_dev, int64_t n_max,
                             const RenderParams &rp, uint32_t *tile_keys, uint32_t *ids,
                             const int64_t *n_inst_dev, int64_t capacity, int32_t *overflow, uint32_t *hist,
                             int hist_bits, int64_t hist_cols, hipStream_t s) {
@@ -633,18 +633,18 @@ hipError_t launch_duplicate(const uint32_t *order, const uint64_t *offsets, cons
     const int window = duplicate_window(capacity);
     const unsigned grid = hist ? (unsigned)hist_cols : std::max(1u, blocks_for(capacity, window));
     if (window == 1024)
-        hipLaunchKernelGGL(duplicate_kernel<1024>, dim3(grid), dim3(kDupNT), 0, s, order, offsets, rect, rec, view_of,
+        hipLaunchKernelGGL(duplicate_kernel<1024>, dim3(grid), dim3(kDupNT), 0, s, order, offsets, rect, rec, chunk_view,
                            n_vis_dev, n_max, rp, tile_keys, ids, n_inst_dev, capacity, overflow, hist, hist_bits);
     else
-        hipLaunchKernelGGL(duplicate_kernel<2048>, dim3(grid), dim3(kDupNT), 0, s, order, offsets, rect, rec, view_of,
+        hipLaunchKernelGGL(duplicate_kernel<2048>, dim3(grid), dim3(kDupNT), 0, s, order, offsets, rect, rec, chunk_view,
                            n_vis_dev, n_max, rp, tile_keys, ids, n_inst_dev, capacity, overflow, hist, hist_bits);
     return hipGetLastError();
 }
 
-hipError_t launch_gather_u32(const uint32_t *src, const uint32_t *idx, uint32_t *dst, const int64_t *n_dev,
+hipError_t launch_gather_view(const uint32_t *chunk_view, const uint32_t *idx, uint32_t *dst, const int64_t *n_dev,
                              int64_t n_max, hipStream_t s) {
     if (n_max > 0)
-        hipLaunchKernelGGL(gather_u32_kernel, dim3(blocks_for(n_max, 256)), dim3(256), 0, s, src, idx, dst, n_dev,
+        hipLaunchKernelGGL(gather_view_kernel, dim3(blocks_for(n_max, 256)), dim3(256), 0, s, chunk_view, idx, dst, n_dev,
                            n_max);
     return hipGetLastError();
 }
