@@ -158,14 +158,15 @@ hipError_t launch_accumulate_counts(const int64_t *n_proc_dev, int64_t n_proc, c
 // sched == NULL: one workgroup per item in item order.  Otherwise sched holds
 // the V * n_tiles items longest list first (launch_tile_order), and workgroup b
 // renders the b-th of them.
-// contrib (optional): contrib[id] = 1 for every processed entry some pixel
-// blends; weight (optional): weight[id] += the entry's summed blend weights
-// alpha T (state and counters are not recorded in either case).
+// contrib (optional): contrib[g] = 1 for every Gaussian some pixel blends;
+// weight (optional): weight[g] += its summed blend weights alpha T, where entry
+// id of view v is Gaussian g = id - v view_stride (no image, state or counters
+// in either case).
 hipError_t launch_composite(const RenderParams &rp, int32_t W, int32_t H, int32_t V, int32_t batch,
                             const uint32_t *ranges, const uint32_t *ids, const Rec2D *rec,
                             float *out_rgb, float *out_T, uint32_t *n_contrib,
                             uint64_t *pair_counter, int32_t pixels_per_thread, uint32_t *sched,
-                            uint8_t *contrib, float *weight, hipStream_t s);
+                            uint8_t *contrib, float *weight, int64_t view_stride, hipStream_t s);
 // bits[w] bit j = (flags[32 w + j] != 0), j < 32, for n flags.
 hipError_t launch_flags_to_bits(const uint8_t *flags, int64_t n, uint32_t *bits, hipStream_t s);
 // Rates measured on the current device (sink: device float[8 x CUs], never

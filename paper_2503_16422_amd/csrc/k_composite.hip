@@ -43,8 +43,9 @@ struct CompArgs {
     int32_t V;                   // views sharing the launch
     const uint32_t *order;       // longest-first schedule: (view, tile) items, longest list first
     int32_t n_items;             // V x tiles per view
-    uint8_t *contrib;            // kMark: per processed entry, set to 1 when blended
-    float *weight;               // kWeight: per processed entry, += sum of alpha T
+    uint8_t *contrib;            // kMark: per Gaussian, set to 1 when blended
+    float *weight;               // kWeight: per Gaussian, += sum of alpha T
+    int64_t view_stride;         // kMark, kWeight: entry of view v - v view_stride = Gaussian
 };
 
 // What a compositor instance records beyond colour and transmittance.
@@ -125,7 +126,7 @@ __device__ __forceinline__ void composite_item(const CompArgs &a, int item, floa
                 const float v = s_side[k];
                 if (v == 0.0f) continue;
                 s_side[k] = 0.0f;
-                const uint32_t id = __float_as_uint(s_rec[3 * k + 2].y);
+                const int64_t id = (int64_t)__float_as_uint(s_rec[3 * k + 2].y) - view * a.view_stride;
                 if constexpr (MARK) a.contrib[id] = 1;
                 else atomicAdd(&a.weight[id], v);
             }
@@ -454,13 +455,13 @@ hipError_t launch_composite(const RenderParams &rp, int32_t W, int32_t H, int32_
                             const uint32_t *ranges, const uint32_t *ids, const Rec2D *rec,
                             float *out_rgb, float *out_T, uint32_t *n_contrib,
                             uint64_t *pair_counter, int32_t ppt, uint32_t *sched, uint8_t *contrib,
-                            float *weight, hipStream_t s) {
+                            float *weight, int64_t view_stride, hipStream_t s) {
     if (ppt != 1 && ppt != 2 && ppt != 4) return hipErrorInvalidValue;
     const int n_tiles = rp.tiles_x * rp.tiles_y * V;
     const bool side = contrib || weight;   // visibility or score pass: no state, no counters
     CompArgs a{rp, W, H, ranges, ids, rec, out_rgb, out_T, side ? nullptr : n_contrib,
                side ? nullptr : reinterpret_cast<unsigned long long *>(pair_counter), ppt, V,
-               sched, n_tiles, contrib, contrib ? nullptr : weight};
+               sched, n_tiles, contrib, contrib ? nullptr : weight, view_stride};
     FDGS_DISPATCH(launch_fwd, a);
     return hipGetLastError();
 }

@@ -116,3 +116,29 @@ def test_variation_score_and_prune_match_oracle(ctx):
         keepmask = np.zeros(sc.n, dtype=bool)
         keepmask[want] = True
         assert np.array_equal(unpacked.astype(bool).ravel()[:sc.n], keepmask)
+
+
+@pytest.mark.parametrize("n", [1, 300, 4096, 9000])
+def test_side_passes_share_launches(ctx, n):
+    """Visibility marks and blend weights over views of two image sizes, which
+    share launches where neighbours agree in size, are those of one call per
+    view: the marks exactly, the weights up to the order of their float32
+    additions (a few hundred per Gaussian at most)."""
+    from paper_2503_16422_amd.render import GaussianModel
+    model = GaussianModel.from_scene(inputs.long_scene(n, seed=21), "cuda:0")
+    sizes = [(96, 80), (96, 80), (203, 60), (96, 80), (96, 80)]
+    cams = [inputs.look_at_camera(0.15 * k, 3.0, w, h) for k, (w, h) in enumerate(sizes)]
+    bits, idx, count = ctx.build_active_mask(model, (), 0.25, 0.5, 2, cams)
+    ref = torch.zeros_like(bits)
+    for cam in cams:
+        for key in (0.25, 0.5):
+            ref |= ctx.build_active_mask(model, (), key, key, 2, [cam])[0]
+    assert torch.equal(bits, ref)
+    keep = torch.tensor([(int(w) >> b) & 1 for w in ref.tolist() for b in range(32)][:n], dtype=torch.bool).nonzero()[:, 0]
+    assert int(count.item()) == keep.numel() and torch.equal(idx[:keep.numel()].cpu().long(), keep)
+    views = [(c, 0.1 * k) for k, c in enumerate(cams)]
+    got = ctx.spatial_score(model, views)
+    one = torch.zeros_like(got)
+    for v in views:
+        ctx.spatial_score(model, [v], out=one)
+    assert torch.allclose(got, one, rtol=1e-5, atol=1e-5)
