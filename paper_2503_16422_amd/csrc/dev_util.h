@@ -22,7 +22,32 @@ __device__ __forceinline__ int64_t xcd_item(int64_t b, int64_t n) {
     return x * q + min(x, r) + b / kXcds;
 }
 
-// Inclusive sum over the 64 lanes of a wavefront.
+// Inclusive sum over the 64 lanes of a wavefront: shifts by 1, 2, 4 and 8
+// within each row of 16 lanes, then row broadcasts 15 and 31, all as DPP
+// operands (six dependent additions; six shuffles through LDS took ten times
+// as long, and nearly every front-end kernel waits for a few of these).  A lane
+// whose source lies outside its row adds 0.  Compiled for the host (the
+// kernels' emulation in the tests), it is the shuffle form.
+#if defined(__AMDGCN__)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint64_t dpp_from(uint64_t v) {
+    return (uint64_t)dpp_from<CTRL, ROW_MASK>((uint32_t)(v >> 32)) << 32 | dpp_from<CTRL, ROW_MASK>((uint32_t)v);
+}
+template <typename T>
+__device__ __forceinline__ T wave_inclusive_sum(T v) {
+    v += dpp_from<0x111, 0xf>(v);    // row_shr:1
+    v += dpp_from<0x112, 0xf>(v);    // row_shr:2
+    v += dpp_from<0x114, 0xf>(v);    // row_shr:4
+    v += dpp_from<0x118, 0xf>(v);    // row_shr:8
+    v += dpp_from<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
+    v += dpp_from<0x143, 0xc>(v);    // row_bcast:31 into rows 2 and 3
+    return v;
+}
+#else
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_sum(T v) {
     const int lane = lane_id();
@@ -33,6 +58,7 @@ __device__ __forceinline__ T wave_inclusive_sum(T v) {
     }
     return v;
 }
+#endif
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -64,28 +90,25 @@ __device__ __forceinline__ float half_sum32(float v) {
     return v;
 }
 // Exclusive sum over a block of NT threads (NT a multiple of 64, <= 1024).
-// `tmp` must hold NT/64 + 1 elements of shared memory.  Returns the thread's
-// exclusive prefix; *total receives the block total.  Contains barriers.
+// `tmp` must hold NT/64 elements of shared memory.  Returns the thread's
+// exclusive prefix; *total receives the block total.  Every thread adds up the
+// wavefronts' totals itself (broadcast reads).  Contains barriers.
 template <int NT, typename T>
 __device__ __forceinline__ T block_exclusive_sum(T v, T *tmp, T *total) {
     constexpr int NW = NT / 64;
     const T inc = wave_inclusive_sum(v);
     if (lane_id() == 63) tmp[wave_id()] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        T run = 0;
-        for (int w = 0; w < NW; ++w) {
-            const T x = tmp[w];
-            tmp[w] = run;
-            run += x;
-        }
-        tmp[NW] = run;
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const T x = tmp[w];
+        if (w < wave_id()) before += x;
+        all += x;
     }
+    *total = all;
     __syncthreads();
-    const T res = tmp[wave_id()] + inc - v;
-    *total = tmp[NW];
-    __syncthreads();
-    return res;
+    return before + inc - v;
 }
 
 }  // namespace fdgs
