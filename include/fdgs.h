@@ -295,7 +295,9 @@ FDGS_API fdgs_status fdgs_render_backward_2d(fdgs_ctx *ctx, fdgs_state *state, c
 FDGS_API fdgs_status fdgs_render_backward_params(fdgs_ctx *ctx, fdgs_state *state, const fdgs_grads *grads,
                                                  hipStream_t stream);
 
-/* Release a state (NULL is accepted). */
+/* Release a state (NULL is accepted).  Synchronises the device, except for a state all of whose passes
+ * ran on the null stream and whose buffers were not handed out (fdgs_state_binning): such a state's
+ * buffers may wait for the context's next new state on the null stream, until fdgs_destroy. */
 FDGS_API fdgs_status fdgs_state_release(fdgs_ctx *ctx, fdgs_state *state);
 
 /*

@@ -145,7 +145,13 @@ void release(Buf &b) {
 }
 
 constexpr int32_t kDefaultPpt = 2;
-constexpr int64_t kBucketMaxN = int64_t(1) << 20;   // largest processed count of a view ordered by buckets
+// Largest processed count of a view ordered by buckets.  Above it most buckets
+// outgrow a workgroup's LDS and the radix sort is the faster (unfiltered frame
+// of 3M).  With a device count (a mask) the bound is the model's size, of which
+// a mask keeps a fraction: a masked frame of 3M Gaussians, 0.8M of them
+// processed, takes 645 us with the radix sort and 611 with buckets.
+constexpr int64_t kBucketMaxN = int64_t(1) << 20;
+constexpr int64_t kBucketMaxMasked = int64_t(1) << 22;
 
 // Several views of one forward pass: device copies of their descriptions and of
 // the view of each chunk of entries, and the largest processed count.
@@ -834,9 +840,10 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     HIP_TRY(ensure(S->order_k2, sizeof(uint32_t) * n_max));
     HIP_TRY(ensure(S->order_v2, sizeof(uint32_t) * n_max));
     HIP_TRY(ensure(S->offsets, sizeof(uint64_t) * n_max));
-    // views of at most kBucketMaxN processed Gaussians: depth order and offsets by buckets (three launches)
+    // views of not too many processed Gaussians: depth order and offsets by buckets (three launches)
     const int64_t n_view_max = vt.views ? vt.max_n : n_max;
-    const bool by_buckets = n_max > 0 && n_view_max <= kBucketMaxN;
+    const bool by_buckets = n_max > 0 && n_view_max <= (n_dev ? kBucketMaxMasked : kBucketMaxN) &&
+                            n_view_max * tiles_per_view < (int64_t(1) << kBucketTileBits);
     size_t bucket_words = 0, bucket_clear = 0;
     if (by_buckets) {
         (void)bucket_work(nullptr, n_view_max, V, &bucket_words, &bucket_clear);

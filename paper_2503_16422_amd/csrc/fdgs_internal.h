@@ -88,9 +88,12 @@ size_t bucket_scratch_words(int64_t n_max);
 hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, const int64_t *n_vis_dev, int64_t n_max,
                                const uint64_t *depth_key, uint32_t *work, uint32_t *alt, uint32_t *bucketed,
                                uint32_t *out, hipStream_t s);
+// A bucket's entries (23 bits) and tiles share a 64-bit word: a view has fewer than 2^23 entries and its
+// entries times the tiles of the image stay below 2^41.
+constexpr int kBucketTileBits = 41;
 // Bucket arrays of V views of at most n_view_max entries: nb = 2^bucket_log2_for(n_view_max) buckets per view.
 struct BucketWork {
-    uint64_t *count;      // per bucket: entries (above bit 43) and their tiles
+    uint64_t *count;      // per bucket: entries (from bit kBucketTileBits on) and their tiles
     uint64_t *view;       // the same per view
     uint64_t *tstart;     // tiles before a bucket
     uint32_t *start;      // entries before a bucket (one more word)

@@ -46,11 +46,15 @@ constexpr int kNT = 256;
 // non-empty bucket (16 views of 225k: count 99 -> 40 us, scatter 35 -> 27 us).
 constexpr int64_t kSmallUpTo = int64_t(1) << 19;
 static_assert(kViewChunk == 16 * kNT, "a workgroup's entries belong to one view");
-// A sorting workgroup is a chain of loads (start, position, depth) and a short
-// ranking: what counts is that all of them (one per bucket, 4096 for a frame)
-// are resident at once, 16 on a CU: 128 threads and under 10 KB of LDS.
-constexpr int kSortNT = 128;
-constexpr int kCap = 384;                  // positions a block sorts in LDS at once
+// A sorting workgroup (NT threads, CAP positions in LDS at once) is a chain of
+// loads (start, position, depth) and a short ranking: what counts is that all
+// of them (one per bucket, 4096 for a frame) are resident at once, 16 on a CU:
+// 128 threads and under 10 KB of LDS.  Above 2^20 entries a bucket holds
+// several hundred and wants the larger form, or it would be sorted in pieces
+// and merged (masked frame of 3M, 0.66M visible: 82 -> 65 us).
+constexpr int kSortNT = 128, kCap = 384;
+constexpr int kLargeNT = 256, kLargeCap = 1024;
+constexpr int64_t kLargeAbove = int64_t(1) << 20;
 
 __device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_max) {
     return n_dev ? min(*n_dev, n_max) : n_max;
@@ -208,23 +212,20 @@ __device__ __forceinline__ Image image_of(const KeyRange &k, uint32_t b, uint32_
     return im;
 }
 
-// An entry's code: bucket (12 bits) and slot (20 bits; a view has at most 2^20
-// entries, and its nearest one is not in the last bucket), or kNoEntry.
-constexpr uint32_t kNoEntry = ~0u;
-constexpr int kSlotBits = 20;
 constexpr int kMaxPer = 4096 / kNT;      // buckets per thread at the largest nb
-// A bucket's (block's, view's) word: entries above, their tiles in the low 43
-// bits (2^20 entries of at most 2^22 tiles).
-constexpr int kTileBits = 43;
+// A bucket's (block's, view's) word: entries above, their tiles in the low
+// kBucketTileBits bits.
+constexpr int kTileBits = kBucketTileBits;
 __device__ __forceinline__ uint32_t entries_of(uint64_t w) { return (uint32_t)(w >> kTileBits); }
 __device__ __forceinline__ uint64_t tiles_of(uint64_t w) { return w & ((uint64_t(1) << kTileBits) - 1); }
 __device__ __forceinline__ uint64_t add64(uint64_t *p, uint64_t v) {
     return atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
 }
 
+// Leaves each entry's bucket + 1 (0: not visible) in `bucket` and its place there in `slot`.
 template <int KPT, typename Src>
 __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb, BucketWork w, const uint32_t *tiles,
-                                                           uint32_t *code) {
+                                                           uint16_t *bucket, uint32_t *slot) {
     extern __shared__ uint64_t s_cnt[];                      // [nb]
     __shared__ uint64_t s_red[kRangeWords];
     __shared__ uint64_t s_tmp[kNT / 64 + 1];
@@ -284,7 +285,9 @@ __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb,
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
         const int64_t j = c.lo + (int64_t)r * kNT + threadIdx.x;
-        if (j < c.hi) code[j] = in[r] ? (bk[r] << kSlotBits | ((uint32_t)s_cnt[bk[r]] + rank[r])) : kNoEntry;
+        if (j >= c.hi) continue;
+        bucket[j] = in[r] ? (uint16_t)(bk[r] + 1u) : (uint16_t)0;
+        if (in[r]) slot[j] = (uint32_t)s_cnt[bk[r]] + rank[r];
     }
     if (w.view) {                                            // uniform: the views' totals
         uint64_t total;
@@ -298,8 +301,8 @@ __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb,
 // total) and the tile sums' scan for the sort.
 template <int KPT, typename Src>
 __global__ void __launch_bounds__(kNT) bucket_scatter_kernel(Src src, uint32_t nb, int V, BucketWork w,
-                                                             const uint32_t *code, uint32_t *out, int64_t n_out,
-                                                             bool tiles, int64_t *counts) {
+                                                             const uint16_t *bucket, const uint32_t *slot,
+                                                             uint32_t *out, int64_t n_out, bool tiles, int64_t *counts) {
     extern __shared__ uint32_t s_start[];                    // [nb]
     __shared__ uint32_t s_tmp[kNT / 64 + 1];
     __shared__ uint64_t s_tmp64[kNT / 64 + 1];
@@ -310,13 +313,14 @@ __global__ void __launch_bounds__(kNT) bucket_scatter_kernel(Src src, uint32_t n
     const uint32_t per = nb >= (uint32_t)kNT ? nb / kNT : 1u;
     const uint32_t b0 = threadIdx.x * per;
     uint64_t cn[kMaxPer];
-    uint32_t cd[KPT], pos[KPT];
+    uint32_t bk[KPT], sl[KPT], pos[KPT];
 #pragma unroll
     for (int k = 0; k < kMaxPer; ++k) cn[k] = count[min(b0 + (uint32_t)k, nb - 1u)];
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
         const int64_t j = c.lo + (int64_t)r * kNT + threadIdx.x;
-        cd[r] = j < c.hi ? code[j] : kNoEntry;
+        bk[r] = j < c.hi ? bucket[j] : 0u;
+        sl[r] = j < c.hi ? slot[j] : 0u;
         pos[r] = j < c.hi ? src.pos(j) : 0u;
     }
     // entries and tiles of the views before
@@ -345,9 +349,9 @@ __global__ void __launch_bounds__(kNT) bucket_scatter_kernel(Src src, uint32_t n
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
-        if (cd[r] == kNoEntry) continue;
-        const uint32_t slot = s_start[min(cd[r] >> kSlotBits, nb - 1u)] + (cd[r] & ((1u << kSlotBits) - 1u));
-        if (slot < (uint64_t)n_out) out[slot] = pos[r];
+        if (bk[r] == 0u) continue;
+        const uint64_t to = (uint64_t)s_start[min(bk[r], nb) - 1u] + sl[r];
+        if (to < (uint64_t)n_out) out[to] = pos[r];
     }
     if (!c.first) return;                                    // uniform
     uint32_t *start = w.start + (size_t)c.v * nb;
@@ -380,9 +384,9 @@ __device__ __forceinline__ bool before(uint64_t da, uint32_t pa, uint64_t db, ui
     return da < db || (da == db && pa < pb);
 }
 
-// One block sorts m <= kCap (key, position) pairs held in LDS by rank:
+// One block sorts m <= CAP (key, position) pairs held in LDS by rank:
 // element e goes to the number of elements that precede it.  Every thread
-// compares its own elements (e = t + kSortNT r) against all m from LDS
+// compares its own elements (e = t + NT r) against all m from LDS
 // broadcasts; wavefronts without elements skip the loop.  The ranks come from
 // 32-bit images of the keys first (Image): two vector instructions per compare
 // and four keys per LDS read, where the 64-bit key with the position takes
@@ -391,12 +395,12 @@ __device__ __forceinline__ bool before(uint64_t da, uint32_t pa, uint64_t db, ui
 // position), which is strict, decides.  s_owner receives each rank's element.
 // Entries [m, m rounded up to 16) of the images and to 8 of the keys are set to
 // all ones, which precede nothing.
-template <int R>
+template <int R, int NT>
 __device__ __forceinline__ void ranks_by_image(const uint32_t *s_img, int m, uint32_t (&rk)[R]) {
     uint32_t ke[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int e = (int)threadIdx.x + kSortNT * r;
+        const int e = (int)threadIdx.x + NT * r;
         ke[r] = e < m ? s_img[e] : 0u;
         rk[r] = 0;
     }
@@ -411,13 +415,13 @@ __device__ __forceinline__ void ranks_by_image(const uint32_t *s_img, int m, uin
             for (int r = 0; r < R; ++r) rk[r] += kf[u] < ke[r] ? 1u : 0u;
     }
 }
-template <int R>
+template <int R, int NT>
 __device__ __forceinline__ void ranks_by_key(const uint64_t *s_key, const uint32_t *s_pos, int m, uint32_t (&rk)[R]) {
     uint64_t ke[R];
     uint32_t pe[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int e = (int)threadIdx.x + kSortNT * r;
+        const int e = (int)threadIdx.x + NT * r;
         ke[r] = e < m ? s_key[e] : ~0ull;
         pe[r] = e < m ? s_pos[e] : ~0u;
         rk[r] = 0;
@@ -437,57 +441,59 @@ __device__ __forceinline__ void ranks_by_key(const uint64_t *s_key, const uint32
             for (int r = 0; r < R; ++r) rk[r] += before(kf[u], pf[u], ke[r], pe[r]) ? 1u : 0u;
     }
 }
-template <int R>
+template <int R, int NT>
 __device__ __forceinline__ void rank_sort_r(const uint64_t *s_key, const uint32_t *s_pos, const uint32_t *s_img, int m,
                                             uint32_t *s_owner, uint32_t *s_twice) {
     uint32_t rk[R];
     auto own = [&]() {
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if ((int)threadIdx.x + kSortNT * r < m) s_owner[rk[r]] = threadIdx.x + kSortNT * r;
+            if ((int)threadIdx.x + NT * r < m) s_owner[rk[r]] = threadIdx.x + NT * r;
         __syncthreads();
     };
-    ranks_by_image<R>(s_img, m, rk);
+    ranks_by_image<R, NT>(s_img, m, rk);
     own();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const uint32_t e = threadIdx.x + kSortNT * r;
+        const uint32_t e = threadIdx.x + NT * r;
         if ((int)e < m && s_owner[rk[r]] != e) *s_twice = 1u;
     }
     __syncthreads();
     if (*s_twice == 0u) return;                            // uniform
-    ranks_by_key<R>(s_key, s_pos, m, rk);
+    ranks_by_key<R, NT>(s_key, s_pos, m, rk);
     own();
 }
 
 // s_owner[rank] = element for the m pairs (contains barriers, the first before any read).
+template <int NT, int CAP>
 __device__ void rank_sort(uint64_t *s_key, uint32_t *s_pos, uint32_t *s_img, int m, uint32_t *s_owner,
                           uint32_t *s_twice) {
-    for (int i = m + (int)threadIdx.x; i < ((m + 15) & ~15); i += kSortNT) s_img[i] = ~0u;
-    for (int i = m + (int)threadIdx.x; i < ((m + 7) & ~7); i += kSortNT) {
+    for (int i = m + (int)threadIdx.x; i < ((m + 15) & ~15); i += NT) s_img[i] = ~0u;
+    for (int i = m + (int)threadIdx.x; i < ((m + 7) & ~7); i += NT) {
         s_key[i] = ~0ull;
         s_pos[i] = ~0u;
     }
     if (threadIdx.x == 0) *s_twice = 0u;
     __syncthreads();
-    if (m <= kSortNT) rank_sort_r<1>(s_key, s_pos, s_img, m, s_owner, s_twice);
-    else if (m <= 2 * kSortNT) rank_sort_r<2>(s_key, s_pos, s_img, m, s_owner, s_twice);
-    else rank_sort_r<kCap / kSortNT>(s_key, s_pos, s_img, m, s_owner, s_twice);
+    if (m <= NT) rank_sort_r<1, NT>(s_key, s_pos, s_img, m, s_owner, s_twice);
+    else if (m <= 2 * NT) rank_sort_r<2, NT>(s_key, s_pos, s_img, m, s_owner, s_twice);
+    else rank_sort_r<CAP / NT, NT>(s_key, s_pos, s_img, m, s_owner, s_twice);
 }
 
 // Block b sorts bucket b; with tiles, offsets[j] = the tiles of the entries
 // before the j-th of the order (from the bucket's tstart).
-__global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *start, const uint32_t *range, uint32_t nb,
+template <int NT, int CAP>
+__global__ void __launch_bounds__(NT) bucket_sort_kernel(const uint32_t *start, const uint32_t *range, uint32_t nb,
                                                               const uint32_t *bucketed, const uint64_t *depth_key,
                                                               int64_t n_max, uint32_t *alt, uint32_t *out,
                                                               const uint32_t *tiles, const uint64_t *tstart,
                                                               uint64_t *offsets) {
-    __shared__ uint64_t s_key[kCap + 8];
-    __shared__ __attribute__((aligned(16))) uint32_t s_img[kCap];
-    __shared__ uint32_t s_pos[kCap + 8], s_tiles[kCap], s_owner[kCap];
+    __shared__ uint64_t s_key[CAP + 8];
+    __shared__ __attribute__((aligned(16))) uint32_t s_img[CAP];
+    __shared__ uint32_t s_pos[CAP + 8], s_tiles[CAP], s_owner[CAP];
     __shared__ uint32_t s_twice;
-    __shared__ uint32_t s_wave[kSortNT / 64];
-    __shared__ uint64_t s_tmp[kSortNT / 64 + 1];
+    __shared__ uint32_t s_wave[NT / 64];
+    __shared__ uint64_t s_tmp[NT / 64 + 1];
     const uint32_t lo = start[blockIdx.x], hi = (uint32_t)min((int64_t)start[blockIdx.x + 1], n_max);
     const uint32_t *r = range + 4 * (size_t)(blockIdx.x / nb);
     const KeyRange kr{r[0], r[1], r[2], r[3]};
@@ -496,10 +502,10 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
     if (m <= 0) return;
     const Image im = image_of(kr, blockIdx.x % nb, nb);
     const uint32_t last = (uint32_t)(n_max - 1);    // positions index depth_key[0, n_max)
-    // sorted runs of kCap (all of the bucket when it fits)
-    for (int64_t c0 = 0; c0 < m; c0 += kCap) {
-        const int len = (int)min((int64_t)kCap, m - c0);
-        for (int i = threadIdx.x; i < len; i += kSortNT) {
+    // sorted runs of CAP (all of the bucket when it fits)
+    for (int64_t c0 = 0; c0 < m; c0 += CAP) {
+        const int len = (int)min((int64_t)CAP, m - c0);
+        for (int i = threadIdx.x; i < len; i += NT) {
             const uint32_t pos = min(bucketed[lo + c0 + i], last);
             const uint64_t key = depth_key[pos];
             s_pos[i] = pos;
@@ -507,20 +513,20 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
             s_img[i] = im.of(key);
             if (tiles) s_tiles[i] = tiles[pos];
         }
-        rank_sort(s_key, s_pos, s_img, len, s_owner, &s_twice);
-        for (int j = threadIdx.x; j < len; j += kSortNT) out[lo + c0 + j] = s_pos[s_owner[j]];
-        if (m <= kCap) break;
+        rank_sort<NT, CAP>(s_key, s_pos, s_img, len, s_owner, &s_twice);
+        for (int j = threadIdx.x; j < len; j += NT) out[lo + c0 + j] = s_pos[s_owner[j]];
+        if (m <= CAP) break;
         __syncthreads();
     }
-    if (m <= kCap) {
+    if (m <= CAP) {
         if (!tiles) return;
         // exclusive sums of the tile counts in the new order: each thread's
         // consecutive elements, the wavefront, the wavefronts before (at most
-        // kCap counts of 2^22 tiles: 32 bits hold the sums)
-        const int per = ((int)m + kSortNT - 1) / kSortNT, j0 = (int)threadIdx.x * per;
-        uint32_t t[kCap / kSortNT], sum = 0;
+        // CAP counts of 2^22 tiles: 32 bits hold the sums)
+        const int per = ((int)m + NT - 1) / NT, j0 = (int)threadIdx.x * per;
+        uint32_t t[CAP / NT], sum = 0;
 #pragma unroll
-        for (int q = 0; q < kCap / kSortNT; ++q) {
+        for (int q = 0; q < CAP / NT; ++q) {
             t[q] = q < per && j0 + q < (int)m ? s_tiles[s_owner[j0 + q]] : 0u;
             sum += t[q];
         }
@@ -530,7 +536,7 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
         uint64_t run = tiles_before + (inc - sum);
         for (int w = 0; w < wave_id(); ++w) run += s_wave[w];
 #pragma unroll
-        for (int q = 0; q < kCap / kSortNT; ++q)
+        for (int q = 0; q < CAP / NT; ++q)
             if (q < per && j0 + q < (int)m) {
                 offsets[lo + j0 + q] = run;
                 run += t[q];
@@ -541,12 +547,12 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
     // the i-th smallest of the two runs, found by a binary search of how many
     // of them come from the first run
     uint32_t *src = out + lo, *dst = alt + lo;
-    for (int64_t w = kCap; w < m; w <<= 1) {
+    for (int64_t w = CAP; w < m; w <<= 1) {
         for (int64_t a0 = 0; a0 < m; a0 += 2 * w) {
             const int64_t la = min(w, m - a0);
             const int64_t lb = max((int64_t)0, min(w, m - a0 - w));
             const uint32_t *A = src + a0, *B = src + a0 + la;
-            for (int64_t i = threadIdx.x; i < la + lb; i += kSortNT) {
+            for (int64_t i = threadIdx.x; i < la + lb; i += NT) {
                 int64_t s = max((int64_t)0, i - lb), e = min(i, la);
                 while (s < e) {
                     const int64_t mid = (s + e) >> 1;
@@ -568,14 +574,14 @@ __global__ void __launch_bounds__(kSortNT) bucket_sort_kernel(const uint32_t *st
         uint32_t *t = src; src = dst; dst = t;
     }
     if (src != out + lo)
-        for (int64_t i = threadIdx.x; i < m; i += kSortNT) out[lo + i] = src[i];
+        for (int64_t i = threadIdx.x; i < m; i += NT) out[lo + i] = src[i];
     if (!tiles) return;
     uint64_t run = tiles_before;
-    for (int64_t j0 = 0; j0 < m; j0 += kSortNT) {
+    for (int64_t j0 = 0; j0 < m; j0 += NT) {
         const int64_t j = j0 + threadIdx.x;
         uint64_t total;
         const uint64_t ex =
-            block_exclusive_sum<kSortNT>(j < m ? (uint64_t)tiles[min(src[j], last)] : uint64_t(0), s_tmp, &total);
+            block_exclusive_sum<NT>(j < m ? (uint64_t)tiles[min(src[j], last)] : uint64_t(0), s_tmp, &total);
         if (j < m) offsets[lo + j] = run + ex;
         run += total;
     }
@@ -620,15 +626,19 @@ template <int KPT, typename Src>
 hipError_t order_buckets(const Src &src, int64_t n_view_max, int32_t V, const BucketWork &w,
                          const uint64_t *depth_key, int64_t n_max, uint32_t *alt, uint32_t *bucketed, uint32_t *out,
                          const uint32_t *tiles, uint64_t *offsets, int64_t *counts, hipStream_t s) {
+    // until the sort writes them, `out` holds the entries' buckets and `alt` their slots
     const uint32_t nb = 1u << bucket_log2_for(n_view_max);
     const int64_t chunks = (n_max + KPT * kNT - 1) / (KPT * kNT);
     hipLaunchKernelGGL((bucket_count_kernel<KPT, Src>), dim3((unsigned)chunks), dim3(kNT),
-                       sizeof(uint64_t) * nb, s, src, nb, w, tiles, alt);
+                       sizeof(uint64_t) * nb, s, src, nb, w, tiles, reinterpret_cast<uint16_t *>(out), alt);
     hipLaunchKernelGGL((bucket_scatter_kernel<KPT, Src>), dim3((unsigned)chunks), dim3(kNT), sizeof(uint32_t) * nb, s, src, nb,
-                       (int)V, w, (const uint32_t *)alt, bucketed, n_max, tiles != nullptr, counts);
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3(nb * (unsigned)V), dim3(kSortNT), 0, s, (const uint32_t *)w.start,
-                       (const uint32_t *)w.range, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles, (const uint64_t *)w.tstart,
-                       offsets);
+                       (int)V, w, reinterpret_cast<const uint16_t *>(out), (const uint32_t *)alt, bucketed, n_max,
+                       tiles != nullptr, counts);
+    const bool large = n_view_max > kLargeAbove;
+    hipLaunchKernelGGL((large ? bucket_sort_kernel<kLargeNT, kLargeCap> : bucket_sort_kernel<kSortNT, kCap>),
+                       dim3(nb * (unsigned)V), dim3(large ? kLargeNT : kSortNT), 0, s, (const uint32_t *)w.start,
+                       (const uint32_t *)w.range, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles,
+                       (const uint64_t *)w.tstart, offsets);
     return hipGetLastError();
 }
 

@@ -667,3 +667,34 @@ def test_fresh_states_beside_other_streams_match_one_stream(ctx):
             assert torch.equal(a, b)
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("kept,twins", [(1, 0), (3000, 0), (40_000, 1500), (900_000, 0)])
+def test_masked_frame_of_a_large_model_orders_as_the_small_one(ctx, kept, twins):
+    """A mask over a model of more than 2^20 Gaussians takes the buckets' large
+    sort; image, tile lists and depths are those of a model that holds only the
+    kept Gaussians (ordered by the small sort).  Twins share one depth, more of
+    them than a workgroup sorts at once."""
+    from paper_2503_16422_amd.render import GaussianModel
+    n = (1 << 20) + 777
+    base = inputs.tiny_scene(max(kept, 1000), seed=31)
+    rng = np.random.default_rng(kept)
+    idx = np.sort(rng.permutation(n)[:kept]).astype(np.int32)
+    small = {k: torch.from_numpy(np.ascontiguousarray(getattr(base, k)[..., :kept])).cuda() for k in GaussianModel.FIELDS}
+    if twins:
+        for k in GaussianModel.FIELDS:
+            small[k][..., :twins] = small[k][..., :1]
+    at = torch.from_numpy(idx).cuda()
+    large = {k: torch.zeros((*v.shape[:-1], n), device="cuda") for k, v in small.items()}
+    for k, v in small.items():
+        large[k][..., at.long()] = v
+    small, large = (GaussianModel(*[d[k] for k in GaussianModel.FIELDS]) for d in (small, large))
+    cam = inputs.look_at_camera(0.1, 3.0, 150, 110)
+    rgb0, _, st0 = ctx.render(small, cam, 0.45, keep_state=True)
+    rgb1, _, st1 = ctx.render(large, cam, 0.45, idx=at, n_idx=torch.tensor([kept], device="cuda"), keep_state=True)
+    b0, b1 = ctx.binning(st0), ctx.binning(st1)
+    st0.release()
+    st1.release()
+    assert b0["n_vis"] == b1["n_vis"] and b0["n_inst"] == b1["n_inst"]
+    assert torch.equal(b0["sorted_ids"], b1["sorted_ids"]) and torch.equal(b0["tile_ranges"], b1["tile_ranges"])
+    assert torch.equal(rgb0, rgb1)
