@@ -1361,9 +1361,9 @@ fdgs_status check_grads(const fdgs_state *S, const fdgs_grads *grads, const char
 fdgs_status enqueue_backward_2d(fdgs_ctx *ctx, fdgs_state *S, const float *dL_drgb, hipStream_t stream) {
     if (stream != nullptr) S->beyond_null_stream = true;
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(ensure(S->g2d, sizeof(float) * kG2dStride * std::max<int64_t>(S->n_max, 1)));
+    HIP_TRY(ensure(S->g2d, sizeof(double) * kG2dStride * std::max<int64_t>(S->n_max, 1)));
     StageTimer tm(ctx, FDGS_STAGE_BWD_COMPOSITE, stream);
-    HIP_TRY(launch_clear_g2d(S->vis_list, S->counts.as<int64_t>(), S->n_max, S->g2d.as<float>(), stream));
+    HIP_TRY(launch_clear_g2d(S->vis_list, S->counts.as<int64_t>(), S->n_max, S->g2d.as<double>(), stream));
     // the adjoint takes the tiles longest list first: the forward's order when it
     // made one, else one made here
     const int32_t n_tiles = S->rp.tiles_x * S->rp.tiles_y;
@@ -1374,7 +1374,7 @@ fdgs_status enqueue_backward_2d(fdgs_ctx *ctx, fdgs_state *S, const float *dL_dr
     }
     HIP_TRY(launch_composite_backward(S->rp, S->W, S->H, S->batch, S->ppt, S->ranges.as<uint32_t>(), S->sorted_ids,
                                       S->rec.as<Rec2D>(), S->T_final.as<float>(), S->n_contrib.as<uint32_t>(),
-                                      dL_drgb, S->g2d.as<float>(), S->n_max, S->sched.as<uint32_t>(), stream));
+                                      dL_drgb, S->g2d.as<double>(), S->n_max, S->sched.as<uint32_t>(), stream));
     S->has_g2d = true;
     return FDGS_OK;
 }
@@ -1386,7 +1386,7 @@ fdgs_status enqueue_backward_params(fdgs_ctx *ctx, fdgs_state *S, const fdgs_gra
     StageTimer tm(ctx, FDGS_STAGE_BWD_PREPROCESS, stream);
     const int64_t *n_proc_dev = S->idx ? S->n_idx_dev : nullptr;
     HIP_TRY(launch_preprocess_backward(kmodel(&S->model), S->idx, n_proc_dev, S->n_max, S->cam, S->t, S->rp,
-                                       S->vis_list, S->counts.as<int64_t>(), S->g2d.as<float>(), *grads, stream));
+                                       S->vis_list, S->counts.as<int64_t>(), S->g2d.as<double>(), *grads, stream));
     return FDGS_OK;
 }
 

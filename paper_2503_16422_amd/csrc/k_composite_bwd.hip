@@ -22,7 +22,7 @@ struct BwdArgs {
     const float *T_final;
     const uint32_t *n_contrib;
     const float *dL;
-    float *g2d;        // [n_proc][kG2dStride]: du, dv, d conic a, b, c, d opacity, d rgb
+    double *g2d;       // [n_proc][kG2dStride]: du, dv, d conic a, b, c, d opacity, d rgb
     const uint32_t *order;   // tiles longest list first (workgroup b takes tile order[b]), or NULL: raster order
 };
 
@@ -50,9 +50,11 @@ struct BwdArgs {
 // wavefront together (wave_sums18), leaving one sum in each of 18 lanes, which
 // add them into the tile's LDS accumulators with one instruction.  After each
 // batch the sums leave the tile as gradients, nine consecutive lanes to the
-// nine values of a Gaussian, which share one 64-byte line of g2d: an atomic
+// nine values of a Gaussian, which share one 128-byte line of g2d: an atomic
 // instruction then touches seven lines, where a thread per Gaussian touched 64
-// lines nine times.  (Fine-tuning frame, 200k Gaussians, 16x16 tiles: adjoint
+// lines nine times.  Over the tiles the gradients add up in float64: a large
+// footprint's terms cancel over hundreds of tiles, and the parameter adjoint
+// amplifies what float32 sums in arbitrary order leave.  (Fine-tuning frame, 200k Gaussians, 16x16 tiles: adjoint
 // 500 -> 245 us, of which the global adds took 190 and the LDS adds 68; training
 // view, 500k, 32x32: 311 -> 224 us.)  A wavefront walks only the records whose
 // footprint ellipse reaches its cell: the others have alpha below alpha_min at
@@ -284,7 +286,8 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
                 else if (j == 5) out = m / s_rec[3 * k + 2].z;                    // d opacity
                 else out = (j == 3 ? -1.0f : -0.5f) * m;                          // d conic a, b, c
             }
-            if (out != 0.0f) atomicAdd(a.g2d + (int64_t)__float_as_uint(s_rec[3 * k + 2].w) * kG2dStride + j, out);
+            if (out != 0.0f)
+                atomicAdd(a.g2d + (int64_t)__float_as_uint(s_rec[3 * k + 2].w) * kG2dStride + j, (double)out);
         }
         __syncthreads();
         for (int i = threadIdx.x; i < cnt * kVals; i += NT) s_acc[i] = 0.0f;
@@ -293,11 +296,11 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
 
 // Zeroes the visible Gaussians' lines of g2d, the only ones the adjoint adds to and reads.
 __global__ void __launch_bounds__(256) clear_g2d_kernel(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max,
-                                                        float4 *g2d) {
-    constexpr int kVec = kG2dStride / 4;
+                                                        double2 *g2d) {
+    constexpr int kVec = kG2dStride / 2;
     const int64_t n = min(*n_vis_dev, n_max) * kVec;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        g2d[(int64_t)vis_list[i / kVec] * kVec + i % kVec] = make_float4(0.f, 0.f, 0.f, 0.f);
+        g2d[(int64_t)vis_list[i / kVec] * kVec + i % kVec] = make_double2(0.0, 0.0);
 }
 
 // Pixels per thread in the adjoint: 1 for 8x8 tiles, else 4 when the forward
@@ -322,7 +325,7 @@ void launch_bwd(const BwdLaunch &l, int n_tiles, hipStream_t s) {
 hipError_t launch_composite_backward(const RenderParams &rp, int32_t W, int32_t H, int32_t batch, int32_t ppt,
                                      const uint32_t *ranges, const uint32_t *ids, const Rec2D *rec,
                                      const float *T_final, const uint32_t *n_contrib,
-                                     const float *dL_drgb, float *g2d, int64_t /*n_proc_max*/,
+                                     const float *dL_drgb, double *g2d, int64_t /*n_proc_max*/,
                                      const uint32_t *order, hipStream_t s) {
     BwdLaunch l{BwdArgs{rp, W, H, ranges, ids, rec, T_final, n_contrib, dL_drgb, g2d, order}, ppt};
     const int n_tiles = rp.tiles_x * rp.tiles_y;
@@ -330,11 +333,11 @@ hipError_t launch_composite_backward(const RenderParams &rp, int32_t W, int32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, float *g2d, hipStream_t s) {
+hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, double *g2d, hipStream_t s) {
     if (n_max == 0) return hipSuccess;
-    const int64_t threads = n_max * (kG2dStride / 4);
+    const int64_t threads = n_max * (kG2dStride / 2);
     hipLaunchKernelGGL(clear_g2d_kernel, dim3((unsigned)std::min<int64_t>((threads + 255) / 256, 2048)), dim3(256), 0, s,
-                       vis_list, n_vis_dev, n_max, reinterpret_cast<float4 *>(g2d));
+                       vis_list, n_vis_dev, n_max, reinterpret_cast<double2 *>(g2d));
     return hipGetLastError();
 }
 
