@@ -51,6 +51,16 @@ struct LoadU32 {
     }
 };
 
+// Values the scan's first pass left in the output array.
+struct LoadKept {
+    const uint64_t *in;
+    template <int K>
+    __device__ __forceinline__ void load(const int64_t (&j)[K], uint64_t (&v)[K]) const {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = in[j[k]];
+    }
+};
+
 // The thread's kItems consecutive elements starting at base, zero past n.
 template <typename Load>
 __device__ __forceinline__ void load_items(const Load &ld, int64_t base, int64_t n, uint64_t (&v)[kItems]) {
@@ -68,9 +78,12 @@ __device__ __forceinline__ void load_items(const Load &ld, int64_t base, int64_t
         if (base + k >= n) v[k] = 0;
 }
 
+// Chunk sums; with keep, the values too (a gather's second pass then reads them
+// in order: offsets of an unfiltered 3M frame 80 -> 63 us, the second pass's
+// gather of 64-byte lines for 4 bytes each gone).
 template <typename Load>
 __global__ void __launch_bounds__(kNT) reduce_kernel(Load ld, const int64_t *n_dev, int64_t n_max,
-                                                     uint64_t *partial) {
+                                                     uint64_t *partial, uint64_t *keep) {
     __shared__ uint64_t tmp[kNT / 64 + 1];
     const int64_t n = count_of(n_dev, n_max);
     const int64_t base = (int64_t)blockIdx.x * kChunk + (int64_t)threadIdx.x * kItems;
@@ -78,7 +91,10 @@ __global__ void __launch_bounds__(kNT) reduce_kernel(Load ld, const int64_t *n_d
     load_items(ld, base, n, v);
     uint64_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) s += v[k];
+    for (int k = 0; k < kItems; ++k) {
+        s += v[k];
+        if (keep && base + k < n) keep[base + k] = v[k];
+    }
     uint64_t total;
     block_exclusive_sum<kNT>(s, tmp, &total);
     if (threadIdx.x == 0) partial[blockIdx.x] = total;
@@ -142,7 +158,7 @@ __global__ void __launch_bounds__(kNT) downsweep_kernel(Load ld, const int64_t *
 
 template <typename Load, typename Out>
 hipError_t scan_impl(Load ld, Out *out, const int64_t *n_dev, int64_t n_max, int64_t *total,
-                     void *scratch, hipStream_t s) {
+                     void *scratch, hipStream_t s, bool keep = false) {   // keep: Out is uint64_t
     const int64_t nb = (n_max + kChunk - 1) / kChunk;
     uint64_t *partial = static_cast<uint64_t *>(scratch);
     if (nb == 0) {
@@ -152,11 +168,16 @@ hipError_t scan_impl(Load ld, Out *out, const int64_t *n_dev, int64_t n_max, int
                            (const uint32_t *)nullptr, (int64_t)0, 1);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((reduce_kernel<Load>), dim3((unsigned)nb), dim3(kNT), 0, s, ld, n_dev, n_max, partial);
+    uint64_t *kept = keep ? reinterpret_cast<uint64_t *>(out) : nullptr;
+    hipLaunchKernelGGL((reduce_kernel<Load>), dim3((unsigned)nb), dim3(kNT), 0, s, ld, n_dev, n_max, partial, kept);
     hipLaunchKernelGGL(top_scan_kernel, dim3(1), dim3(kTopNT), 0, s, partial, nb, total, (uint32_t *)nullptr,
                        (int64_t)0, (uint32_t *)nullptr, (const uint32_t *)nullptr, (int64_t)0, 1);
-    hipLaunchKernelGGL((downsweep_kernel<Load, Out>), dim3((unsigned)nb), dim3(kNT), 0, s, ld, n_dev,
-                       n_max, (const uint64_t *)partial, out);
+    if (kept)
+        hipLaunchKernelGGL((downsweep_kernel<LoadKept, Out>), dim3((unsigned)nb), dim3(kNT), 0, s, LoadKept{kept}, n_dev,
+                           n_max, (const uint64_t *)partial, out);
+    else
+        hipLaunchKernelGGL((downsweep_kernel<Load, Out>), dim3((unsigned)nb), dim3(kNT), 0, s, ld, n_dev,
+                           n_max, (const uint64_t *)partial, out);
     return hipGetLastError();
 }
 
@@ -313,7 +334,7 @@ hipError_t scan_flags_u8(const uint8_t *in, uint32_t *out, const int64_t *n_dev,
 hipError_t scan_u32_to_u64(const uint32_t *in, const uint32_t *gather, uint64_t *out,
                            const int64_t *n_dev, int64_t n_max, int64_t *total, void *scratch,
                            hipStream_t s) {
-    return scan_impl(LoadU32{in, gather}, out, n_dev, n_max, total, scratch, s);
+    return scan_impl(LoadU32{in, gather}, out, n_dev, n_max, total, scratch, s, gather != nullptr);
 }
 
 hipError_t compact_visible(const uint8_t *visible, const uint64_t *depth_key, const int64_t *n_dev, int64_t n_max,
@@ -331,7 +352,7 @@ hipError_t compact_visible(const uint8_t *visible, const uint64_t *depth_key, co
     } else {
         if (nb > 0)
             hipLaunchKernelGGL((reduce_kernel<LoadU8>), dim3((unsigned)nb), dim3(kNT), 0, s, LoadU8{visible}, n_dev,
-                               n_max, partial);
+                               n_max, partial, (uint64_t *)nullptr);
         hipLaunchKernelGGL(top_scan_kernel, dim3(1), dim3(kTopNT), 0, s, partial, nb, total, clear, n_clear, range,
                            (const uint32_t *)nullptr, (int64_t)0, 1);
     }
