@@ -78,11 +78,11 @@ hipError_t compact_visible(const uint8_t *visible, const uint64_t *depth_key, co
                            int64_t n_clear, uint32_t *range, void *scratch, hipStream_t s,
                            const uint32_t *vis_count = nullptr);
 
-// Depth order of one view's visible entries by bucketing and per-bucket sorts: out[0..n_vis) = the
-// positions (vals) ordered by (depth_key[pos], pos).  work holds bucket_scratch_words(n_max) words:
-// counts and cursors (words [0, 2 nb), cleared by compact_visible), bucket starts, and the key range
-// (words 3 nb + 1 and 3 nb + 2, filled by compact_visible).  bucketed and alt are scratch of n_max
-// words; none of the arrays may alias.
+// Depth order of a compacted list of one view's visible entries by bucketing and per-bucket sorts:
+// out[0..n_vis) = the positions (vals) ordered by (depth_key[pos], pos).  work holds
+// bucket_scratch_words(n_max) words: the buckets' 64-bit counts (words [0, 2 nb), zero before the call),
+// bucket starts, the key range (words 3 nb + 1 and 3 nb + 2, filled by compact_visible) and four more.
+// bucketed and alt are scratch of n_max words; none of the arrays may alias.
 int bucket_log2_for(int64_t n_max);
 size_t bucket_scratch_words(int64_t n_max);
 hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, const int64_t *n_vis_dev, int64_t n_max,

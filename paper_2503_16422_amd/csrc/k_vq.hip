@@ -63,7 +63,7 @@ constexpr int kScreenWaves = 4;
 constexpr int kColTiles = 2;                   // 32-Gaussian tiles per wavefront
 constexpr int kScreenRows = kScreenWaves * kColTiles * 32;   // Gaussians per workgroup
 constexpr int kStage = 2;                      // entry tiles per LDS stage
-constexpr int kScreenPerCu = 3;                // workgroups a CU holds (146 registers)
+constexpr int kScreenPerCu = 3;                // workgroups a CU holds (168 registers)
 constexpr int kScreenGroups = 256 * kScreenPerCu;
 constexpr float kLowest = -3e38f;              // below every score, and finite with any low bits
 
