@@ -875,8 +875,8 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
         StageTimer tm(ctx, FDGS_STAGE_COMPACT, stream);
         if (need_state) HIP_TRY(ensure(S->vis_pos, sizeof(uint32_t) * n_max));
         HIP_TRY(compact_visible(S->visible.as<uint8_t>(), S->depth_key.as<uint64_t>(), n_dev, n_max, counts + 0,
-                                S->order_k.as<uint32_t>(), S->order_v.as<uint32_t>(),
-                                need_state ? S->vis_pos.as<uint32_t>() : nullptr, nullptr, 0, nullptr, S->scratch.p,
+                                by_buckets ? nullptr : S->order_k.as<uint32_t>(),
+                                by_buckets ? nullptr : S->order_v.as<uint32_t>(), need_state ? S->vis_pos.as<uint32_t>() : nullptr, nullptr, 0, nullptr, S->scratch.p,
                                 stream, vis_count));
     }
     uint32_t *ov = nullptr;

@@ -68,7 +68,7 @@ hipError_t scan_u32_to_u64(const uint32_t *in, const uint32_t *gather, uint64_t 
                            const int64_t *n_dev, int64_t n_max, int64_t *total,
                            void *scratch, hipStream_t s);
 // Visible entries in order -> keys32 = float32 bits of their depth, vals = position (and, when asc is
-// not NULL, asc = position too: a copy the depth sort does not overwrite); *total = count.  Before the
+// not NULL, asc = position too: a copy the depth sort does not overwrite; keys32 and vals NULL: asc only); *total = count.  Before the
 // entries are written, clear[0..n_clear) is zeroed and range (when not NULL) receives the [min, max]
 // of the keys.  vis_count (may be NULL): the preprocess's visible count per workgroup of
 // kPreprocessBlock entries (ceil(n_max / kPreprocessBlock) of them), which replaces the scan's

@@ -182,8 +182,8 @@ hipError_t scan_impl(Load ld, Out *out, const int64_t *n_dev, int64_t n_max, int
 }
 
 // Visible compaction: the downsweep of a scan over the visible flags that
-// writes each visible entry's (float32 depth bits, position) to its slot and,
-// when range is given, folds the keys into range = [min, max] (positive
+// writes each visible entry's (float32 depth bits, position) to its slot (only
+// its position, to asc, when keys32 is null) and, when range is given, folds the keys into range = [min, max] (positive
 // floats: bit order is value order).
 __global__ void __launch_bounds__(kNT) compact_visible_kernel(const uint8_t *visible, const uint64_t *depth_key,
                                                               const int64_t *n_dev, int64_t n_max,
@@ -205,13 +205,15 @@ __global__ void __launch_bounds__(kNT) compact_visible_kernel(const uint8_t *vis
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         if (v[k]) {
-            const double z = __longlong_as_double((long long)depth_key[base + k]);
-            const uint32_t key = __float_as_uint((float)z);   // z > 0: bit order = value order
-            keys32[run] = key;
-            vals[run] = (uint32_t)(base + k);
+            if (keys32) {
+                const double z = __longlong_as_double((long long)depth_key[base + k]);
+                const uint32_t key = __float_as_uint((float)z);   // z > 0: bit order = value order
+                keys32[run] = key;
+                vals[run] = (uint32_t)(base + k);
+                kmin = min(kmin, key);
+                kmax = max(kmax, key);
+            }
             if (asc) asc[run] = (uint32_t)(base + k);
-            kmin = min(kmin, key);
-            kmax = max(kmax, key);
             ++run;
         }
     }
