@@ -40,11 +40,13 @@ namespace fdgs {
 namespace {
 
 constexpr int kNT = 256;
-// Entries per thread (KPT) of a counting / scattering workgroup: 4 up to 2^19
-// entries, so that a frame's ~140k still fill the chip, 16 above (whole view
-// chunks), where what counts is the global adds, one per workgroup and
-// non-empty bucket (16 views of 225k: count 99 -> 40 us, scatter 35 -> 27 us).
-constexpr int64_t kSmallUpTo = int64_t(1) << 19;
+// Entries per thread (KPT) of a counting / scattering workgroup: 4 up to 2^18
+// entries, so that a frame's ~140k still fill the chip (masked frame of 200k:
+// count and scatter 24 us, 27 with 16), 16 above (whole view chunks), where what
+// counts is each workgroup's own setting up and the global adds, one per
+// workgroup and non-empty bucket (a view of 500k: count and scatter 35 -> 30 us;
+// 16 views of 225k: 134 -> 67 us).
+constexpr int64_t kSmallUpTo = int64_t(1) << 18;
 static_assert(kViewChunk == 16 * kNT, "a workgroup's entries belong to one view");
 // A sorting workgroup (NT threads, CAP positions in LDS at once) is a chain of
 // loads (start, position, depth) and a short ranking: what counts is that all
