@@ -273,3 +273,44 @@ def test_released_states_are_reused_safely(ctx, side_stream):
         assert torch.equal(rgb, ref[k % 3][0])
         for name in NAMES:
             assert same_up_to_atomic_order(g[name], ref[k % 3][1][name]), (k, name)
+
+
+@pytest.mark.parametrize("tile,batch,ppt", [((8, 8), 64, 1), ((16, 16), 128, 2), ((32, 32), 256, 2), ((16, 16), 64, 4),
+                                            ((32, 32), 256, 4)])
+def test_thin_footprints_log_scale_gradient_elementwise(ctx, tile, batch, ppt):
+    """Axis-aligned footprints of 0.05 to 0.3 px under the dilation, apart from
+    each other and at every offset from the pixel rows, under a gradient of one
+    sign: the second moment in y that leads to log_scale[1] then sums about 50
+    terms of one sign, however many pixels a thread has.  The terms' own errors
+    (3e-7, the exponent's roundings) average out to 4e-8 and the ten levels of
+    sums add 2^-25 each in random walk (9e-8): half of the elements are within
+    2^-23 of the float64 gradient and every one within five times that."""
+    from paper_2503_16422_amd.render import GaussianModel
+    w, h, step, z = 256, 192, 16, 4.0
+    rng = np.random.default_rng(21)
+    f = 400.0
+    cam = inputs.Camera(np.eye(3), np.array([0.0, 0.0, z]), f, f, w / 2, h / 2, w, h, 0.01)
+    u, v = [a.ravel() for a in np.meshgrid(np.arange(step // 2, w, step), np.arange(step // 2, h, step))]
+    n = u.size
+    u = u + rng.uniform(-0.5, 0.5, n)
+    v = v + rng.uniform(-2.0, 2.0, n)
+    px = z / f                                             # world units per pixel
+    sc = inputs.tiny_scene(n, seed=1)
+    sc.mean[:] = [(u - w / 2) * px, (v - h / 2) * px, np.zeros(n), np.full(n, 0.5)]
+    sc.log_scale[:] = np.log([np.full(n, 1.5 * px), rng.uniform(0.05, 0.3, n) * px, np.full(n, 0.2 * px), np.full(n, 1.0)])
+    for q in (sc.q_left, sc.q_right):
+        q[:] = np.array([1.0, 0.0, 0.0, 0.0])[:, None]
+    sc.opacity_logit[:] = 1.5
+    sc.sh[1:] = 0.0
+    sc.sh[0] = 0.8
+    cfg = _lib.default_cfg(tile_w=tile[0], tile_h=tile[1], batch=batch, pixels_per_thread=ppt)
+    model = GaussianModel.from_scene(sc, "cuda:0")
+    rgb, _, state = ctx.render(model, cam, 0.5, cfg, keep_state=True)
+    grads = ctx.backward(state, torch.ones_like(rgb), model)
+    torch.cuda.synchronize()
+    ctx.release(state)
+    ref = og.render_vjp(sc.arrays(), cam, 0.5, oracle_settings(cfg), np.ones((3, h, w)))["log_scale"][1]
+    err = np.abs(grads["log_scale"][1].cpu().numpy() - ref) / np.abs(ref)
+    print(f"ppt {ppt}: median {np.median(err):.2e}, largest {err.max():.2e}")
+    assert np.median(err) <= 2.0 ** -23, np.median(err)
+    assert err.max() <= 5 * 2.0 ** -23, err.max()
