@@ -53,8 +53,12 @@ constexpr float kKappa = 6.4e-5f;
 constexpr float kHalfKappa = 0.5f * kKappa;
 // Flushed denormals: an absolute error far below this.
 constexpr float kTiny = 0x1p-100f;
-// Squared norms from here on go to the exact kernel (no product of the rest overflows).
+// Entries of this squared norm and above, or without a finite one, are left out of the
+// screening (no product of the rest with a vector below kSure overflows).
 constexpr float kHuge = 0x1p100f;
+// The screening decides only for vectors and nearest entries of squared norms below
+// this: an entry left out is then more than (2^50 - 2^45)^2 away, the nearest at most (2^46)^2.
+constexpr float kSure = 0x1p90f;
 
 constexpr int kEnt = 32;                       // entries per matrix tile (rows)
 constexpr int kSteps = kD / 16;                // products of depth 16 per tile
@@ -66,6 +70,7 @@ constexpr int kStage = 2;                      // entry tiles per LDS stage
 constexpr int kScreenPerCu = 3;                // workgroups a CU holds (168 registers)
 constexpr int kScreenGroups = 256 * kScreenPerCu;
 constexpr float kLowest = -3e38f;              // below every score, and finite with any low bits
+constexpr float kFloor = -0x1p110f;            // scores of entries that take part lie above it
 
 // code[j][d] = sh plane d at Gaussian init[j] (indices clamped into the model)
 __global__ void __launch_bounds__(kNT) vq_gather_kernel(const float *sh, int64_t n, const uint32_t *init,
@@ -113,33 +118,41 @@ __device__ __forceinline__ void split_bf16(const float (&v)[8], bf16x8 *hi, bf16
 // One wavefront per tile of 32 entries: their fragments in the order the
 // matrix instruction takes them (lane l: entry l % 32, components
 // 16 s + 8 (l / 32) + 0..7), their squared norms, and what is added to a row's
-// products, -(1/2 - kappa/2) |c|^2 (kLowest for the rows past k).  Block 0 clears the
-// counter of open Gaussians.
+// products, -(1/2 - kappa/2) |c|^2 (kLowest for the rows past k).  An entry whose
+// squared norm is kHuge or more, infinite or NaN counts as such a row (zeros and
+// kLowest): a score of its own could be infinite or NaN and would displace the
+// running best.  Block 0 clears the counter of open Gaussians.
 __global__ void __launch_bounds__(64) vq_frag_kernel(const float *code, int64_t k, bf16x8 *frag, float *start,
                                                      float *norm2, uint32_t *n_open) {
     const int lane = threadIdx.x;
     if (blockIdx.x == 0 && lane == 0) *n_open = 0u;
     const int64_t j = (int64_t)blockIdx.x * kEnt + lane % 32;
     double sum = 0.0;
+    float v[kSteps][8];
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-        float v[8];
+    for (int s = 0; s < kSteps; ++s)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            v[q] = j < k ? code[j * kD + 16 * s + 8 * (lane / 32) + q] : 0.0f;
-            sum += (double)v[q] * (double)v[q];
+            v[s][q] = j < k ? code[j * kD + 16 * s + 8 * (lane / 32) + q] : 0.0f;
+            sum += (double)v[s][q] * (double)v[s][q];
         }
+    sum += __shfl_xor(sum, 32, 64);
+    const float n2 = (float)sum;
+    const bool in = j < k && n2 < kHuge;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        if (!in)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[s][q] = 0.0f;
         bf16x8 hi, lo;
-        split_bf16(v, &hi, &lo);
+        split_bf16(v[s], &hi, &lo);
         bf16x8 *dst = frag + ((int64_t)blockIdx.x * kSteps + s) * 2 * 64;
         dst[lane] = hi;
         dst[64 + lane] = lo;
     }
-    sum += __shfl_xor(sum, 32, 64);
     if (lane < 32) {
-        const float n2 = (float)sum;
         norm2[j] = n2;                                  // padded to whole tiles
-        start[j] = j < k ? fmaxf(-(0.5f - kHalfKappa) * n2, kLowest) : kLowest;
+        start[j] = in ? -(0.5f - kHalfKappa) * n2 : kLowest;
     }
 }
 
@@ -323,8 +336,9 @@ __global__ void __launch_bounds__(kScreenWaves * 64, kScreenPerCu) vq_screen_ker
 // Per Gaussian, over its block's places: the entry j* of the largest a is the nearest
 // one for certain when a_j* - a_j > kappa (|x|^2 + |c_j*|^2) for the second
 // largest a_j (then |x|^2 - 2 D_j - kappa/2 ... exceeds j*'s bound for every
-// other entry).  Otherwise -- also for any NaN, and for norms so large that a
-// product could have overflowed -- the Gaussian joins the open list; its
+// other entry).  Otherwise -- also for any NaN, for norms so large that a product
+// could have overflowed, and where no entry took part (the largest a is then a
+// padding row's, below kFloor) -- the Gaussian joins the open list; its
 // assignment holds the top bit and its place there, and its best starts as
 // (inf, entry 0), what the exact search returns when no distance is finite.
 constexpr uint32_t kOpen = 0x80000000u;
@@ -347,7 +361,7 @@ __global__ void __launch_bounds__(kNT) vq_resolve_kernel(const float *in1, const
             merge_top(m1, m2, j, in1[o], in2[o], inj[o]);
         }
         const float xn = x_norm2[i], cn = c_norm2[j];
-        const bool sure = m1 - m2 > kKappa * (xn + cn) * 1.001f + kTiny && xn < kHuge && cn < kHuge;
+        const bool sure = m1 - m2 > kKappa * (xn + cn) * 1.001f + kTiny && m1 > kFloor && xn < kSure && cn < kSure;
         open = !sure;
         if (sure) assign[i] = j;
     }

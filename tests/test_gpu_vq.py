@@ -179,3 +179,33 @@ def test_assignment_is_the_nearest_in_float32(ctx, n, k, kind):
     if kind == "twins":
         c = code.cpu().numpy()                     # equal entries: always the lowest of them
         assert all(not (c[:a[i]] == c[a[i]]).all(axis=1).any() for i in range(a.size))
+
+
+@pytest.mark.parametrize("n,k,iterations", [(1, 1, 0), (40, 1, 1), (300, 1, 2), (65, 2, 1), (700, 33, 0), (700, 33, 2),
+                                            (300, 64, 1)])
+@pytest.mark.parametrize("what", [np.nan, np.inf, 3e38, 1e30])
+def test_codebooks_without_a_usable_entry(ctx, n, k, iterations, what):
+    """Every entry (k <= 2), or all but two, starts from a Gaussian with a NaN, an
+    infinite or an enormous coefficient; the others are of ordinary size or 1e10.  With
+    one cluster a NaN also gets in by the first mean.  The assignment is the float32
+    search's over the codebook returned (no finite distance: entry 0), never an entry
+    past it; tolerance as above."""
+    sc = inputs.tiny_scene(n, seed=n + k)
+    rng = np.random.default_rng(n + k)
+    sc.sh[:, :, ::3] *= np.float32(1e10)
+    order = rng.permutation(n)[:min(n, k)]
+    init = np.resize(order, k)
+    bad = order if k <= 2 else order[2:]
+    sc.sh[rng.integers(0, 16), rng.integers(0, 3), bad] = what
+    model = model_of(sc)
+    code, assign = ctx.sh_kmeans(model, k, iterations, init_index=torch.from_numpy(init.astype(np.int32)).cuda())
+    torch.cuda.synchronize()
+    a = assign.cpu().numpy()
+    assert a.min() >= 0 and a.max() < k
+    with np.errstate(over="ignore"):
+        d = chain_distances(vq.sh_vectors(sc.sh), code.cpu().numpy())
+    d = np.where(np.isnan(d), np.float32(np.inf), d)
+    low = d.min(axis=1)
+    got = d[np.arange(d.shape[0]), a]
+    assert np.all((got <= np.nextafter(low, np.float32(np.inf))) | np.isinf(low))
+    assert np.all(a[np.isinf(low)] == 0)
