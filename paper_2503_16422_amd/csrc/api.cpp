@@ -154,12 +154,14 @@ constexpr int64_t kBucketMaxN = int64_t(1) << 20;
 constexpr int64_t kBucketMaxMasked = int64_t(1) << 22;
 
 // Several views of one forward pass: device copies of their descriptions and of
-// the view of each chunk of entries, and the largest processed count.
+// the view of each chunk of entries, the largest processed count and their sum
+// (without the padding of the chunks).
 struct ViewTable {
     const ViewDesc *views = nullptr;
     const uint32_t *chunk_view = nullptr;
     int32_t V = 1;
     int64_t max_n = 0;
+    int64_t n_proc = 0;
 };
 
 bool valid_tile(int w, int h) {
@@ -961,7 +963,7 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     if (ctx->prof && !ctx->capturing) {
         HIP_TRY(ensure(ctx->prof_acc, 5 * sizeof(uint64_t)));
         acc = ctx->prof_acc.as<uint64_t>();
-        HIP_TRY(launch_accumulate_counts(n_dev, n_total, counts, capacity, acc, stream));
+        HIP_TRY(launch_accumulate_counts(n_dev, vt.views ? vt.n_proc : n_total, counts, capacity, acc, stream));
     }
     {
         StageTimer tm(ctx, FDGS_STAGE_COMPOSITE, stream);
@@ -1100,6 +1102,7 @@ fdgs_status run_side_views(fdgs_ctx *ctx, const fdgs_model *model, const SidePas
             vt.chunk_view = reinterpret_cast<const uint32_t *>(vt.views + V);
             vt.V = V;
             vt.max_n = n;
+            vt.n_proc = n * V;
             st = run_forward(ctx, &ctx->scratch_state, nullptr, vt, nullptr, stride * V, W, H, &c, nullptr, nullptr,
                              false, stream, contrib, weight);
             if (st == FDGS_ERR_HIP || st == FDGS_ERR_CAPACITY) {
@@ -1132,7 +1135,7 @@ fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_vi
     for (int32_t c = 0; c < n_launch; ++c) {
         const int32_t v0 = c * per_launch, V = std::min(per_launch, n_views - v0);
         std::vector<ViewDesc> table(V);
-        int64_t off = 0, max_n = 0;
+        int64_t off = 0, max_n = 0, sum_n = 0;
         for (int32_t k = 0; k < V; ++k) {
             const fdgs_view &w = views[v0 + k];
             ViewDesc &d = table[k];
@@ -1144,6 +1147,7 @@ fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_vi
             d.p_off = off;
             off += padded_entries(d.n_proc);
             max_n = std::max(max_n, d.n_proc);
+            sum_n += d.n_proc;
         }
         if (off >= (int64_t(1) << 32))
             return fail(FDGS_ERR_CAPACITY, "fdgs_render_batch: %lld Gaussians in one launch exceed 2^32",
@@ -1164,6 +1168,7 @@ fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_vi
             vt.chunk_view = reinterpret_cast<const uint32_t *>(vt.views + V);
             vt.V = V;
             vt.max_n = max_n;
+            vt.n_proc = sum_n;
             if (fdgs_status st = run_forward(ctx, &ctx->batch_state, nullptr, vt, nullptr, off, W, H, cfg,
                                              out_rgb + v0 * img, nullptr, false, stream))
                 return st;

@@ -165,3 +165,21 @@ def test_batched_workload_at_full_size(ctx):
         ref = oc.render(scenes[s].arrays(), cam, t, st, idx=sel, mode="rect")
         worst, nflag = compare_image(host[k], ref, label=f"batched 800x800 view {k}")
         print(f"batched view {k} (scene {picks[s]}): max err {worst:.2e}, flagged {nflag}")
+
+
+def test_profile_counts_processed_entries_without_padding(ctx, batch_setup):
+    """The profile's processed count of batched views (uneven, one empty, one
+    entry) and of the score pass, whose views share launches, is the sum of the
+    views' own entries."""
+    _, models, _ = batch_setup
+    cam = inputs.batch_cameras(120, 96)[0]
+    idx = torch.arange(2000, dtype=torch.int32, device="cuda")
+    views = [(0, cam, 0.5, idx, 0), (0, cam, 0.5, idx, 1), (1, cam, 0.4), (0, cam, 0.3, idx, 1999), (2, cam, 0.6)]
+    ctx.profile(True)
+    ctx.render_batch(models, views)
+    batch = ctx.profile_read(reset=True)["processed"]
+    ctx.spatial_score(models[1], [(cam, 0.2), (cam, 0.5), (cam, 0.8)])
+    side = ctx.profile_read(reset=True)["processed"]
+    ctx.profile(False)
+    assert batch == 0 + 1 + 5000 + 1999 + 9000
+    assert side == 3 * 5000
