@@ -19,6 +19,7 @@ using namespace fdgs;
 namespace {
 
 thread_local std::string g_err;
+thread_local hipError_t g_hip_error = hipSuccess;   // what the last FDGS_ERR_HIP of HIP_TRY was
 
 constexpr int kMaskMaxFrames = 256;   // frame times of one keyframe window
 constexpr int kMaskMaxViews = 64;     // mask cameras
@@ -36,8 +37,10 @@ fdgs_status fail(fdgs_status code, const char *fmt, ...) {
 #define HIP_TRY(expr)                                                                      \
     do {                                                                                   \
         hipError_t e_ = (expr);                                                            \
-        if (e_ != hipSuccess)                                                              \
+        if (e_ != hipSuccess) {                                                            \
+            g_hip_error = e_;                                                              \
             return fail(FDGS_ERR_HIP, "%s failed: %s", #expr, hipGetErrorString(e_));      \
+        }                                                                                  \
     } while (0)
 
 struct Buf {
@@ -558,9 +561,12 @@ std::vector<unsigned char> view_table_bytes(const std::vector<ViewDesc> &table, 
 // 9.8 -> 4.0 ms; pruning scores of 1M Gaussians over 8 views, 4 per launch: 3.6
 // -> 2.4 ms).  cfg null: the defaults, with 32x32 tiles where that leaves enough
 // of them -- marks and weights don't depend on the tiling, and larger tiles
-// make fewer instances.
+// make fewer instances.  Views that don't fit into memory together run one by one.
 constexpr int64_t kSideEntries = int64_t(1) << 22;
 constexpr int64_t kSideTiles = 2048;
+// Tiles of the views of one launch (12 bytes of lists and order each): enough that
+// only images past 8192 x 8192 pixels in 16x16 tiles are alone for it.
+constexpr int64_t kSideMostTiles = int64_t(1) << 22;
 struct SidePass {
     const fdgs_camera *cams;
     int32_t n_cams;
@@ -1068,53 +1074,88 @@ fdgs_status check_batch(const fdgs_model *scenes, int32_t n_scenes, const fdgs_v
 fdgs_status run_side_views(fdgs_ctx *ctx, const fdgs_model *model, const SidePass &pass, const fdgs_render_cfg *cfg,
                            const fdgs_render_cfg &defaults, uint8_t *contrib, float *weight, hipStream_t stream) try {
     const int64_t n = model->n, stride = padded_entries(n);
-    int64_t most = std::max<int64_t>(kSideEntries / stride, 1);
-    for (int64_t p0 = 0; p0 < pass.size();) {
-        const int32_t W = pass.cam(p0).width, H = pass.cam(p0).height;
+    auto desc = [&](int64_t p, int64_t at) {
+        ViewDesc d;
+        d.m = kmodel(model);
+        d.cam = kcam(&pass.cam(p));
+        d.t = pass.time(p);
+        d.idx = nullptr;
+        d.p_off = at * stride;
+        d.n_proc = n;
+        return d;
+    };
+    auto tiles = [&](int64_t p) {
+        const int32_t tw = (cfg ? cfg : &defaults)->tile_w, th = (cfg ? cfg : &defaults)->tile_h;
+        return (int64_t)((pass.cam(p).width + tw - 1) / tw) * ((pass.cam(p).height + th - 1) / th);
+    };
+    // the groups that share a launch, and their view tables one after another
+    struct Group {
+        int64_t p0;
+        int32_t V;
+        size_t table;
+    };
+    std::vector<Group> groups;
+    std::vector<unsigned char> bytes;
+    for (int64_t p = 0; p < pass.size();) {
+        const int64_t most = std::max<int64_t>(std::min(kSideEntries / stride, kSideMostTiles / tiles(p)), 1);
+        Group g{p, 0, bytes.size()};
         std::vector<ViewDesc> table;
-        for (int64_t p = p0; p < pass.size() && (int64_t)table.size() < most && pass.cam(p).width == W &&
-                             pass.cam(p).height == H; ++p) {
-            ViewDesc d;
-            d.m = kmodel(model);
-            d.cam = kcam(&pass.cam(p));
-            d.t = pass.time(p);
-            d.idx = nullptr;
-            d.p_off = (int64_t)table.size() * stride;
-            d.n_proc = n;
-            table.push_back(d);
+        for (; p < pass.size() && g.V < most && pass.cam(p).width == pass.cam(g.p0).width &&
+               pass.cam(p).height == pass.cam(g.p0).height; ++p)
+            table.push_back(desc(p, g.V++));
+        if (g.V > 1) {
+            const std::vector<unsigned char> t = view_table_bytes(table, stride * g.V);
+            bytes.insert(bytes.end(), t.begin(), t.end());
+            bytes.resize((bytes.size() + 15) / 16 * 16);
         }
-        const int32_t V = (int32_t)table.size();
-        fdgs_render_cfg c = cfg ? *cfg : defaults;
-        if (!cfg && (int64_t)((W + 31) / 32) * ((H + 31) / 32) * V >= kSideTiles) {
-            c.tile_w = c.tile_h = 32;
-            c.batch = 256;
-        }
-        fdgs_status st;
-        if (V == 1) {
-            st = run_forward(ctx, &ctx->scratch_state, &table[0], ViewTable(), nullptr, n, W, H, &c, nullptr, nullptr,
-                             false, stream, contrib, weight);
+        groups.push_back(g);
+    }
+    bool together = true;
+    if (!bytes.empty()) {
+        const hipError_t e = ensure(ctx->side_table, bytes.size());
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            together = false;
         } else {
-            const std::vector<unsigned char> bytes = view_table_bytes(table, stride * V);
-            HIP_TRY(ensure(ctx->side_table, bytes.size()));
+            HIP_TRY(e);
             HIP_TRY(hipMemcpyAsync(ctx->side_table.p, bytes.data(), bytes.size(), hipMemcpyHostToDevice, stream));
-            ViewTable vt;
-            vt.views = ctx->side_table.as<ViewDesc>();
-            vt.chunk_view = reinterpret_cast<const uint32_t *>(vt.views + V);
-            vt.V = V;
-            vt.max_n = n;
-            vt.n_proc = n * V;
-            st = run_forward(ctx, &ctx->scratch_state, nullptr, vt, nullptr, stride * V, W, H, &c, nullptr, nullptr,
-                             false, stream, contrib, weight);
-            if (st == FDGS_ERR_HIP || st == FDGS_ERR_CAPACITY) {
-                // no room for the views' buffers or instances together (nothing is marked or
-                // added before they are all there): one at a time
-                (void)hipGetLastError();
-                most = 1;
-                continue;
-            }
+            HIP_TRY(hipStreamSynchronize(stream));   // `bytes` may go
         }
-        if (st) return st;
-        p0 += V;
+    }
+    for (const Group &g : groups) {
+        const int32_t W = pass.cam(g.p0).width, H = pass.cam(g.p0).height;
+        auto cfg_for = [&](int32_t V) {
+            fdgs_render_cfg c = cfg ? *cfg : defaults;
+            if (!cfg && (int64_t)((W + 31) / 32) * ((H + 31) / 32) * V >= kSideTiles) {
+                c.tile_w = c.tile_h = 32;
+                c.batch = 256;
+            }
+            return c;
+        };
+        if (g.V > 1 && together) {
+            ViewTable vt;
+            vt.views = reinterpret_cast<const ViewDesc *>(ctx->side_table.as<unsigned char>() + g.table);
+            vt.chunk_view = reinterpret_cast<const uint32_t *>(vt.views + g.V);
+            vt.V = g.V;
+            vt.max_n = n;
+            vt.n_proc = n * g.V;
+            const fdgs_render_cfg c = cfg_for(g.V);
+            const fdgs_status st = run_forward(ctx, &ctx->scratch_state, nullptr, vt, nullptr, stride * g.V, W, H, &c,
+                                               nullptr, nullptr, false, stream, contrib, weight);
+            if (st == FDGS_OK) continue;
+            // no room for the views' buffers or instances together: one at a time from here on
+            // (both are found out before the compositor, which marks and adds, is enqueued)
+            if (st != FDGS_ERR_CAPACITY && !(st == FDGS_ERR_HIP && g_hip_error == hipErrorOutOfMemory)) return st;
+            (void)hipGetLastError();
+            together = false;
+        }
+        for (int64_t p = g.p0; p < g.p0 + g.V; ++p) {
+            const ViewDesc one = desc(p, 0);
+            const fdgs_render_cfg c = cfg_for(1);
+            if (fdgs_status st = run_forward(ctx, &ctx->scratch_state, &one, ViewTable(), nullptr, n, W, H, &c, nullptr,
+                                             nullptr, false, stream, contrib, weight))
+                return st;
+        }
     }
     return FDGS_OK;
 } catch (const std::bad_alloc &) {

@@ -142,3 +142,24 @@ def test_side_passes_share_launches(ctx, n):
     for v in views:
         ctx.spatial_score(model, [v], out=one)
     assert torch.allclose(got, one, rtol=1e-5, atol=1e-5)
+
+
+def test_score_pass_over_more_tiles_than_one_launch_can_number(ctx):
+    """512 views of 16384 x 16384 pixels in 8x8 tiles are 2^31 tiles, one more than
+    fits a launch's numbering; each view alone is in order.  The pass takes them
+    in smaller groups and scores the Gaussians that one view scores.  (2^31
+    workgroups: about 20 s.  The sums themselves, 10^6 float32 additions each,
+    have no tight bound.)"""
+    from paper_2503_16422_amd import _lib
+    from paper_2503_16422_amd.render import GaussianModel
+    sc = inputs.tiny_scene(16, seed=3)
+    sc.log_scale[:3] -= 1.0
+    sc.log_scale[3] = 1.0
+    model = GaussianModel.from_scene(sc, "cuda:0")
+    cfg = _lib.default_cfg(tile_w=8, tile_h=8, batch=64, pixels_per_thread=1, schedule=0)
+    view = (inputs.look_at_camera(0.0, 3.0, 16384, 16384), 0.5)
+    one = ctx.spatial_score(model, [view], cfg)
+    assert float(one.max()) > 0
+    many = ctx.spatial_score(model, [view] * 512, cfg)
+    assert torch.equal(many > 0, one > 0)
+    assert torch.all(many >= one)
