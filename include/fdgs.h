@@ -297,7 +297,8 @@ FDGS_API fdgs_status fdgs_render_backward_params(fdgs_ctx *ctx, fdgs_state *stat
 
 /* Release a state (NULL is accepted).  Synchronises the device, except for a state all of whose passes
  * ran on the null stream and whose buffers were not handed out (fdgs_state_binning): such a state's
- * buffers may wait for the context's next new state on the null stream, until fdgs_destroy. */
+ * buffers may wait for the context's next new state on the null stream, until fdgs_destroy.  A released
+ * handle stays unknown to every call. */
 FDGS_API fdgs_status fdgs_state_release(fdgs_ctx *ctx, fdgs_state *state);
 
 /*

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -180,6 +181,7 @@ int bits_for(int64_t v) {   // bits needed to represent values in [0, v)
 }  // namespace
 
 struct fdgs_state {
+    fdgs_state *handle = nullptr;   // what the caller holds (new_handle)
     fdgs_ctx *owner = nullptr;
     bool has_forward = false;
     bool has_g2d = false;   // a backward's first phase ran since the last forward
@@ -242,19 +244,27 @@ namespace {
 // its order is then the only one there is to keep.  At most kSpareStates and
 // kSpareLimit bytes over all contexts; given back by fdgs_destroy and by an
 // allocation that runs out of memory.
+// The caller's name of a state: a number that comes once per process, so that a
+// released name stays unknown whichever state its buffers serve next.
+fdgs_state *new_handle() {
+    static std::atomic<uintptr_t> next{64};
+    return reinterpret_cast<fdgs_state *>(next.fetch_add(16));
+}
+
 std::mutex g_spare_mu;
 constexpr int kSpareStates = 8;
 fdgs_state *g_spare[kSpareStates];   // oldest first
 int g_n_spare = 0;
 constexpr size_t kSpareLimit = size_t(1) << 30;
 
-// Keeps the state; false when there is no room for it.
+// Keeps the state, which then belongs to whoever takes it; false when there is no room for it.
 bool keep_spare(fdgs_state *s, int32_t device) {
     std::lock_guard<std::mutex> lk(g_spare_mu);
     size_t total = s->bytes();
     for (int k = 0; k < g_n_spare; ++k) total += g_spare[k]->bytes();
     if (g_n_spare == kSpareStates || total > kSpareLimit) return false;
     s->device = device;
+    s->has_forward = false;
     g_spare[g_n_spare++] = s;
     return true;
 }
@@ -534,9 +544,9 @@ KCam kcam(const fdgs_camera *c) {
     return k;
 }
 
-fdgs_state *find_state(fdgs_ctx *ctx, fdgs_state *s) {
+fdgs_state *find_state(fdgs_ctx *ctx, fdgs_state *handle) {
     for (fdgs_state *x : ctx->states)
-        if (x == s) return x;
+        if (x->handle == handle) return x;
     return nullptr;
 }
 
@@ -1018,8 +1028,9 @@ fdgs_status fdgs_render_forward(fdgs_ctx *ctx, const fdgs_model *model, const ui
             if (!S) S = new (std::nothrow) fdgs_state();
             if (!S) return fail(FDGS_ERR_HIP, "%s: out of host memory", fn);
             S->owner = ctx;
+            S->handle = new_handle();
             ctx->states.push_back(S);
-            *keep_state = S;
+            *keep_state = S->handle;
         }
     }
     HIP_TRY(hipSetDevice(ctx->device));
@@ -1473,18 +1484,14 @@ fdgs_status fdgs_render_backward_params(fdgs_ctx *ctx, fdgs_state *state, const 
 fdgs_status fdgs_state_release(fdgs_ctx *ctx, fdgs_state *state) {
     if (!ctx) return fail(FDGS_ERR_INVALID_ARG, "fdgs_state_release: ctx is NULL");
     if (!state) return FDGS_OK;
-    auto it = std::find(ctx->states.begin(), ctx->states.end(), state);
-    if (it == ctx->states.end()) return fail(FDGS_ERR_STATE, "fdgs_state_release: unknown state");
-    if (!state->beyond_null_stream && keep_spare(state, ctx->device)) {
-        state->has_forward = false;
-        ctx->states.erase(it);
-        return FDGS_OK;
-    }
+    fdgs_state *S = find_state(ctx, state);
+    if (!S) return fail(FDGS_ERR_STATE, "fdgs_state_release: unknown state");
+    ctx->states.erase(std::find(ctx->states.begin(), ctx->states.end(), S));
+    if (!S->beyond_null_stream && keep_spare(S, ctx->device)) return FDGS_OK;
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
-    state->free_all();
-    delete state;
-    ctx->states.erase(it);
+    S->free_all();
+    delete S;
     return FDGS_OK;
 }
 

@@ -314,3 +314,28 @@ def test_thin_footprints_log_scale_gradient_elementwise(ctx, tile, batch, ppt):
     print(f"ppt {ppt}: median {np.median(err):.2e}, largest {err.max():.2e}")
     assert np.median(err) <= 2.0 ** -23, np.median(err)
     assert err.max() <= 5 * 2.0 ** -23, err.max()
+
+
+def test_a_released_handle_stays_unknown(ctx):
+    """The handle of a released state is refused by release, adjoint and forward
+    also while a later state uses its buffers, and leaves that state alone."""
+    from paper_2503_16422_amd.render import GaussianModel, State
+    model = GaussianModel.from_scene(scene_small(500, seed=17), "cuda:0")
+    cam = inputs.look_at_camera(0.0, 3.0, 48, 48)
+    seen = []
+    for k in range(4):
+        rgb, _, st = ctx.render(model, cam, 0.5, keep_state=True)
+        ref = ctx.backward(st, rgb, model)
+        for old in seen:
+            for call in (lambda s: ctx.release(s), lambda s: ctx.backward(s, rgb, model),
+                         lambda s: ctx.render(model, cam, 0.5, keep_state=s)):
+                with pytest.raises(_lib.FdgsError) as e:
+                    call(State(ctx, type(st.handle)(old), st.shape))
+                assert e.value.code == _lib.FDGS_ERR_STATE
+        again = ctx.backward(st, rgb, model)
+        for name in NAMES:
+            assert same_up_to_atomic_order(again[name], ref[name]), name
+        seen.append(st.handle.value)
+        st.release()
+    assert len(set(seen)) == 4
+    torch.cuda.synchronize()
