@@ -189,7 +189,7 @@ struct fdgs_state {
     // per processed Gaussian
     Buf rec, depth_key, rect, tiles, visible, vis_pos, order_k, order_v, order_k2, order_v2, offsets;
     Buf bucket;        // depth buckets (BucketWork)
-    Buf vis_count;     // per preprocess workgroup: visible entries, then their key ranges
+    Buf vis_count;     // per preprocess workgroup: sampled keys, key ranges, numbers of visible entries
     // per instance
     Buf tkeys, tids, tkeys2, tids2;
     // per tile / pixel
@@ -879,10 +879,11 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     int64_t *counts = S->counts.as<int64_t>();
 
     const int64_t pre_blocks = (n_total + kPreprocessBlock - 1) / kPreprocessBlock;
-    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * 3 * (size_t)pre_blocks));
-    uint32_t *vis_count = S->vis_count.as<uint32_t>(), *block_range = vis_count + pre_blocks;
+    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * 7 * (size_t)pre_blocks));
+    uint32_t *samples = S->vis_count.as<uint32_t>(), *block_range = samples + 4 * pre_blocks;
+    uint32_t *vis_count = block_range + 2 * pre_blocks;
     PreprocOut po{S->rec.as<Rec2D>(), S->depth_key.as<uint64_t>(), S->rect.as<int32_t>(), S->tiles.as<uint32_t>(),
-                  S->visible.as<uint8_t>(), vis_count, block_range, S->bucket.as<uint32_t>(),
+                  S->visible.as<uint8_t>(), vis_count, block_range, samples, S->bucket.as<uint32_t>(),
                   by_buckets ? (int64_t)bucket_clear : 0};
     {
         StageTimer tm(ctx, FDGS_STAGE_PREPROCESS, stream);
@@ -904,7 +905,7 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
         HIP_TRY(depth_order_views(S->visible.as<uint8_t>(), S->depth_key.as<uint64_t>(), S->tiles.as<uint32_t>(),
                                   block_range, n_dev, n_max, vt.views, vt.chunk_view, V, n_view_max,
                                   S->bucket.as<uint32_t>(), S->order_v.as<uint32_t>(), S->order_k2.as<uint32_t>(), ov,
-                                  S->offsets.as<uint64_t>(), counts, stream));
+                                  S->offsets.as<uint64_t>(), counts, stream, samples));
     } else {
         StageTimer tm(ctx, FDGS_STAGE_DEPTH_SORT, stream);
         int alt = 0;

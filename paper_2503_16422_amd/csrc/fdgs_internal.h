@@ -36,6 +36,7 @@ struct PreprocOut {
     uint8_t *visible;    // [P]
     uint32_t *vis_count; // [ceil(P / kPreprocessBlock)] visible entries per workgroup, or NULL
     uint32_t *block_range;   // [2 ceil(P / kPreprocessBlock)] [min, max] float32 depth bits of a workgroup's visible entries
+    uint32_t *samples;       // [4 ceil(P / kPreprocessBlock)], 16-byte aligned: those of one visible entry of each wavefront (~0: none)
     uint32_t *clear;     // [n_clear] words the launch zeroes
     int64_t n_clear;
 };
@@ -81,7 +82,7 @@ hipError_t compact_visible(const uint8_t *visible, const uint64_t *depth_key, co
 // Depth order of a compacted list of one view's visible entries by bucketing and per-bucket sorts:
 // out[0..n_vis) = the positions (vals) ordered by (depth_key[pos], pos).  work holds
 // bucket_scratch_words(n_max) words: the buckets' 64-bit counts (words [0, 2 nb), zero before the call),
-// bucket starts, the key range (words 3 nb + 1 and 3 nb + 2, filled by compact_visible) and four more.
+// bucket starts, the key range (words 3 nb + 1 and 3 nb + 2, filled by compact_visible) and bounds.
 // bucketed and alt are scratch of n_max words; none of the arrays may alias.
 int bucket_log2_for(int64_t n_max);
 size_t bucket_scratch_words(int64_t n_max);
@@ -97,7 +98,7 @@ struct BucketWork {
     uint64_t *view;       // the same per view
     uint64_t *tstart;     // tiles before a bucket
     uint32_t *start;      // entries before a bucket (one more word)
-    uint32_t *range;      // per view: lowest and highest key, and the part of them that the buckets divide
+    uint32_t *edge;       // per view: lowest key of each bucket, and the highest of all
 };
 // Lays them out in `words` (null: sizes only); the first *n_clear of *n_words words have to be zero before
 // depth_order_views.
@@ -108,7 +109,8 @@ BucketWork bucket_work(uint32_t *words, int64_t n_view_max, int32_t V, size_t *n
 hipError_t depth_order_views(const uint8_t *visible, const uint64_t *depth_key, const uint32_t *tiles,
                              const uint32_t *block_range, const int64_t *n_dev, int64_t n_total, const ViewDesc *table,
                              const uint32_t *chunk_view, int32_t V, int64_t n_view_max, uint32_t *work, uint32_t *alt,
-                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s);
+                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s,
+                             const uint32_t *samples = nullptr);
 hipError_t compact_bits(const uint32_t *bits, int64_t n, uint32_t *idx, int64_t *count,
                         void *scratch, hipStream_t s);
 size_t compact_scratch_bytes(int64_t n);

@@ -6,8 +6,8 @@
 // digit pass).  Here three kernels produce the same order, and with it the
 // exclusive sums of the tile counts that the emission needs:
 //   1. count: each visible key (float32 depth bits, a monotone image of the
-//      float64 depth) falls into one of NB buckets of its view, spread linearly
-//      over the range that holds nearly all keys (KeyRange); per-block LDS
+//      float64 depth) falls into one of NB buckets of its view, shared out over
+//      the key range by a sample of the keys (KeyMap); per-block LDS
 //      counts and tile sums (one 64-bit word), one global add per non-empty bucket.  The adds
 //      return the block's place in each bucket, so every entry leaves with its
 //      bucket and its slot there.  The order inside a bucket depends on the scheduling
@@ -20,8 +20,8 @@
 //      repair is needed -- by ranking them in LDS, and sums their tile counts
 //      in that order.  A bucket larger than the LDS tile (many Gaussians at one
 //      depth) is sorted in LDS-sized chunks that the block then merges pairwise
-//      through a second buffer (each output element placed by a binary search
-//      of its co-rank).
+//      through a second buffer (each thread places a run of the output, found
+//      by a binary search of its start's co-rank).
 // The bucket map is monotone in the key, so buckets in index order hold
 // increasing depths and the concatenation of the sorted buckets is the
 // sorted sequence.
@@ -62,10 +62,84 @@ __device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_max)
     return n_dev ? min(*n_dev, n_max) : n_max;
 }
 
-// A view's key range [kmin, kmax] and the part [lo, hi] of it that the buckets
-// divide; the first and the last bucket also take what lies outside.
-struct KeyRange {
-    uint32_t kmin, kmax, lo, hi;
+// How the nb buckets divide a view's key range [kmin, kmax].  Evenly, a dense
+// slab of the scene (a wall seen from the front, a far background) or a few far
+// outliers leave most buckets empty while the rest crowd, and ranking a bucket
+// costs its square.  So the range is cut into even bins, and each gets buckets by
+// its share of a sample of the keys (three quarters of them) and by its width (a
+// quarter).  A heavy bin (an eighth of the sample or more, and four times its
+// even share) is cut once more, the same way; what is not cut further divides its
+// buckets evenly.  The sample is one visible entry of each wavefront of up to
+// kSampleBlocks preprocess workgroups, lanes and workgroups taken by a hash: how
+// the entries are ordered in memory does not matter.  Every workgroup computes the same division.
+// Depth order of 200k entries, even depths: 45 us, stored by depth 35 us; 90% of
+// them in a slab of 1% of the depth 53 us, of 0.01% 120 us; all equal 30 ms.
+// (Dividing the mean range of the workgroups instead: 46 us, 30 ms stored by
+// depth, the slabs 6 and 54 ms; dividing the whole range evenly: the slabs 5 and
+// 42 ms.)
+constexpr int kBins = 128, kSub = 64, kHeavy = 8;
+constexpr int kSampleBlocks = 2 * kNT;
+struct MapTables {
+    uint32_t base[kBins + 1];             // buckets before a bin
+    uint32_t heavy[kBins];                // a heavy bin's place in sub, or ~0
+    uint32_t sub[kHeavy][kSub + 1];       // buckets before a part of the bin, from its first
+    uint32_t n_heavy, which[kHeavy];      // the heavy bins, in any order
+    uint32_t hist[kBins];
+    uint32_t sub_hist[kHeavy][kSub];
+};
+struct KeyMap {
+    uint32_t kmin, kmax, nb;
+    uint32_t bins;              // at most kBins
+    double scale;               // bins per key
+    const MapTables *t;
+    // Position of a key in units of bins, and its bin.
+    __device__ __forceinline__ double at(uint32_t key, uint32_t *c) const {
+        const double x = (double)(max(key, kmin) - kmin) * scale;
+        *c = min((uint32_t)x, bins - 1u);
+        return x;
+    }
+    // Monotone map of a key to [0, nb).
+    __device__ __forceinline__ uint32_t bucket(uint32_t key) const {
+        uint32_t c;
+        double x = at(key, &c) - (double)c;
+        uint32_t first = t->base[c], n = t->base[c + 1] - first;
+        const uint32_t h = t->heavy[c];
+        if (h != ~0u) {
+            x *= (double)kSub;
+            const uint32_t q = min((uint32_t)x, (uint32_t)kSub - 1u);
+            x -= (double)q;
+            n = t->sub[h][q + 1] - t->sub[h][q];
+            first += t->sub[h][q];
+        }
+        return min(first + min((uint32_t)(x * (double)n), max(n, 1u) - 1u), nb - 1u);
+    }
+    // Lowest key of bucket b, to within two.
+    __device__ __forceinline__ uint32_t edge(uint32_t b) const {
+        if (b == 0u) return kmin;
+        if (b >= nb) return kmax;
+        uint32_t lo = 0, hi = bins - 1u;                     // the last bin with base[c] < b
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (t->base[mid] < b) lo = mid; else hi = mid - 1;
+        }
+        const uint32_t h = t->heavy[lo];
+        double x = (double)lo;
+        uint32_t first = t->base[lo], n = t->base[lo + 1] - first;
+        if (h != ~0u) {
+            b -= first;
+            uint32_t l = 0, u = kSub - 1;
+            while (l < u) {
+                const uint32_t mid = (l + u + 1) >> 1;
+                if (t->sub[h][mid] < b) l = mid; else u = mid - 1;
+            }
+            first = t->sub[h][l];
+            n = t->sub[h][l + 1] - first;
+            x += ((double)l + (double)(b - first) / (double)n) / (double)kSub;
+        } else {
+            x += (double)(b - first) / (double)n;
+        }
+        return kmin + (uint32_t)fmin(x / scale, (double)(kmax - kmin));
+    }
 };
 
 // Entries [lo, hi) of the view v that chunk c holds (none: hi <= lo), and
@@ -74,6 +148,7 @@ struct Chunk {
     int v;
     bool first;
     int64_t lo, hi;
+    uint32_t chunk, n_chunks;    // its number among the view's chunks that hold entries
 };
 
 struct SrcList {
@@ -82,15 +157,21 @@ struct SrcList {
     int64_t n_max;
     const uint32_t *zrange;   // [min, max] of the keys
     __device__ __forceinline__ Chunk chunk(int64_t c, int64_t size) const {
-        return Chunk{0, c == 0, c * size, min((c + 1) * size, count_of(n_dev, n_max))};
+        const int64_t n = count_of(n_dev, n_max);
+        return Chunk{0, c == 0, c * size, min((c + 1) * size, n), (uint32_t)c, (uint32_t)((n + size - 1) / size)};
     }
     __device__ __forceinline__ bool load(int64_t j, uint32_t *key) const {
         *key = keys32[j];
         return true;
     }
     __device__ __forceinline__ uint32_t pos(int64_t j) const { return vals[j]; }
-    __device__ __forceinline__ KeyRange range(const Chunk &, uint64_t *) const {
-        return KeyRange{zrange[0], zrange[1], zrange[0], zrange[1]};
+    // The key range, the thread's eight sampled keys (~0: none) and about how many all threads have.
+    __device__ __forceinline__ void range(const Chunk &, uint64_t *, uint32_t *kmin, uint32_t *kmax,
+                                          uint32_t (&sample)[8], uint32_t *sampled) const {
+        *sampled = 0;
+        *kmin = zrange[0];
+        *kmax = zrange[1];
+        for (uint32_t &k : sample) k = ~0u;
     }
 };
 
@@ -98,6 +179,7 @@ struct SrcViews {
     const uint8_t *visible;
     const uint64_t *depth_key;
     const uint32_t *block_range;   // [min, max] key of each preprocess workgroup's visible entries
+    const uint32_t *samples;       // [4] keys of each preprocess workgroup (~0: none), or null: its range's ends
     const int64_t *n_dev;          // one view (table null): device count
     int64_t n_max;
     const ViewDesc *table;
@@ -112,7 +194,8 @@ struct SrcViews {
         } else {
             n = count_of(n_dev, n_max);
         }
-        return Chunk{v, c * size == base, c * size, min((c + 1) * size, base + n)};
+        return Chunk{v, c * size == base, c * size, min((c + 1) * size, base + n), (uint32_t)(c - base / size),
+                     (uint32_t)((n + size - 1) / size)};
     }
     __device__ __forceinline__ bool load(int64_t j, uint32_t *key) const {
         const uint64_t d = depth_key[j];
@@ -120,78 +203,124 @@ struct SrcViews {
         return visible[j] != 0;
     }
     __device__ __forceinline__ uint32_t pos(int64_t j) const { return (uint32_t)j; }
-    // From the preprocess workgroups' ranges (contains barriers).  A few far
-    // outliers stretch [kmin, kmax] so that most buckets stay empty and the rest
-    // crowd (masked frame of 143k: mean bucket of an entry 160, largest 289),
-    // and ranking a bucket costs its square.  The divided part is the mean
-    // workgroup's range, which covers all but a percent, widened by 0.35 of its
-    // width on both sides.
-    __device__ __forceinline__ KeyRange range(const Chunk &w, uint64_t *s_red) const {
+    // From the preprocess workgroups' ranges and samples (contains a barrier).
+    __device__ __forceinline__ void range(const Chunk &w, uint64_t *s_red, uint32_t *kmin, uint32_t *kmax,
+                                          uint32_t (&sample)[8], uint32_t *sampled) const {
         const int64_t base = table ? table[w.v].p_off : 0;
         const int64_t n = table ? table[w.v].n_proc : count_of(n_dev, n_max);
         const int64_t b0 = base / kPreprocessBlock, b1 = (base + n + kPreprocessBlock - 1) / kPreprocessBlock;
+        const uint32_t stride = (uint32_t)((b1 - b0 + kSampleBlocks - 1) / kSampleBlocks);
+        *sampled = 4u * (uint32_t)min(b1 - b0, (int64_t)kSampleBlocks);
+#pragma unroll
+        for (int q = 0; q < kSampleBlocks / kNT; ++q) {
+            const uint32_t s = threadIdx.x + (uint32_t)q * kNT;
+            const int64_t b = b0 + (int64_t)s * stride + ((s * 2654435761u) >> 12) % stride;
+            uint4 k = make_uint4(~0u, ~0u, ~0u, ~0u);
+            if (b < b1) {
+                if (samples) {
+                    k = reinterpret_cast<const uint4 *>(samples)[b];
+                } else if (block_range[2 * b] <= block_range[2 * b + 1]) {
+                    k.x = block_range[2 * b];
+                    k.y = block_range[2 * b + 1];
+                }
+            }
+            sample[4 * q] = k.x;
+            sample[4 * q + 1] = k.y;
+            sample[4 * q + 2] = k.z;
+            sample[4 * q + 3] = k.w;
+        }
         uint32_t lo = ~0u, hi = 0u;
-        uint64_t lo_sum = 0, hi_sum = 0, cnt = 0;
         for (int64_t b = b0 + threadIdx.x; b < b1; b += kNT) {
-            const uint32_t l = block_range[2 * b], h = block_range[2 * b + 1];
-            if (l > h) continue;                             // nothing visible
-            lo = min(lo, l);
-            hi = max(hi, h);
-            lo_sum += l;
-            hi_sum += h;
-            ++cnt;
+            lo = min(lo, block_range[2 * b]);                // nothing visible: [~0, 0]
+            hi = max(hi, block_range[2 * b + 1]);
         }
         uint64_t both = (uint64_t)lo << 32 | (uint32_t)~hi;  // both halves want their minimum
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             const uint64_t o = __shfl_xor(both, off, 64);
             both = (uint64_t)min((uint32_t)(both >> 32), (uint32_t)(o >> 32)) << 32 | min((uint32_t)both, (uint32_t)o);
-            lo_sum += __shfl_xor(lo_sum, off, 64);
-            hi_sum += __shfl_xor(hi_sum, off, 64);
-            cnt += __shfl_xor(cnt, off, 64);
         }
-        if (lane_id() == 0) {
-            uint64_t *r = s_red + 4 * wave_id();
-            r[0] = both;
-            r[1] = lo_sum;
-            r[2] = hi_sum;
-            r[3] = cnt;
-        }
+        if (lane_id() == 0) s_red[wave_id()] = both;
         __syncthreads();
-        KeyRange k{~0u, 0u, 0u, 0u};
-        lo_sum = hi_sum = cnt = 0;
+        lo = ~0u;
+        hi = 0u;
 #pragma unroll
         for (int q = 0; q < kNT / 64; ++q) {
-            k.kmin = min(k.kmin, (uint32_t)(s_red[4 * q] >> 32));
-            k.kmax = max(k.kmax, ~(uint32_t)s_red[4 * q]);
-            lo_sum += s_red[4 * q + 1];
-            hi_sum += s_red[4 * q + 2];
-            cnt += s_red[4 * q + 3];
+            lo = min(lo, (uint32_t)(s_red[q] >> 32));
+            hi = max(hi, ~(uint32_t)s_red[q]);
         }
-        const int64_t l = (int64_t)(lo_sum / max(cnt, (uint64_t)1)), h = (int64_t)(hi_sum / max(cnt, (uint64_t)1));
-        const int64_t more = (h - l) / 3 + 1;
-        k.lo = (uint32_t)max((int64_t)k.kmin, l - more);
-        k.hi = (uint32_t)min((int64_t)k.kmax, h + more);
-        return k;
+        *kmin = lo;
+        *kmax = hi;
     }
 };
 
-constexpr int kRangeWords = 4 * (kNT / 64);      // 64-bit words of LDS that range() needs
-
-// Monotone map of a key to [0, nb).
-__device__ __forceinline__ uint32_t bucket_of(uint32_t key, const KeyRange &k, double scale, uint32_t nb) {
-    const double x = fmin((double)(max(key, k.lo) - k.lo) * scale, (double)(nb - 1u));
-    return (uint32_t)x;
+// The view's map, its tables in *t (s_red: scratch; contains barriers).  Of n
+// buckets, before the k-th of `parts` parts that `before` of `all` samples precede:
+__device__ __forceinline__ uint32_t share_of(uint32_t n, uint32_t before, uint32_t all, uint32_t k, uint32_t parts) {
+    const double by_width = (double)k / (double)parts;       // parts: a power of two
+    return (uint32_t)((double)n * (all ? 0.75 * ((double)before / (double)all) + 0.25 * by_width : by_width));
+}
+template <typename Src>
+__device__ __forceinline__ KeyMap key_map(const Src &src, const Chunk &w, uint32_t nb, MapTables *t, uint64_t *s_red) {
+    const uint32_t i = threadIdx.x;
+    for (uint32_t k = i; k < kHeavy * kSub; k += kNT) t->sub_hist[k / kSub][k % kSub] = 0u;
+    if (i < kBins) t->hist[i] = 0u;
+    if (i == 0) t->n_heavy = 0u;
+    KeyMap m;
+    uint32_t sample[8], sampled;
+    src.range(w, s_red, &m.kmin, &m.kmax, sample, &sampled);
+    // sixteen samples a bin (fewer say little), eight bins at least
+    m.bins = kBins;
+    while (m.bins > 8u && m.bins * 16u > sampled) m.bins >>= 1;
+    m.nb = nb;
+    m.t = t;
+    m.scale = m.kmax >= m.kmin ? (double)m.bins / ((double)(m.kmax - m.kmin) + 1.0) : 0.0;
+    __syncthreads();
+    uint32_t c[8];
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        c[q] = ~0u;
+        if (sample[q] == ~0u) continue;
+        x[q] = m.at(sample[q], &c[q]);
+        atomicAdd(&t->hist[c[q]], 1u);
+    }
+    __syncthreads();
+    const uint32_t mine = i < m.bins ? t->hist[i] : 0u;
+    uint32_t all;
+    const uint32_t before = block_exclusive_sum<kNT>(mine, reinterpret_cast<uint32_t *>(s_red), &all);
+    if (i <= m.bins) t->base[i] = i == m.bins ? nb : share_of(nb, before, all, i, m.bins);
+    if (i < m.bins) {
+        const bool heavy = mine * min(m.bins / 4u, (uint32_t)kHeavy) >= all && all;   // at most kHeavy of them
+        const uint32_t h = heavy ? atomicAdd(&t->n_heavy, 1u) : ~0u;
+        t->heavy[i] = h;
+        if (heavy) t->which[h] = i;
+    }
+    __syncthreads();
+    if (t->n_heavy) {                                        // uniform
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (c[q] != ~0u && t->heavy[c[q]] != ~0u)
+                atomicAdd(&t->sub_hist[t->heavy[c[q]]][min((uint32_t)((x[q] - (double)c[q]) * (double)kSub),
+                                                           (uint32_t)kSub - 1u)], 1u);
+        __syncthreads();
+        for (uint32_t h = (uint32_t)wave_id(); h < t->n_heavy; h += kNT / 64) {
+            const uint32_t b = t->which[h];
+            const uint32_t n = t->base[b + 1] - t->base[b], v = t->sub_hist[h][lane_id()];
+            t->sub[h][lane_id()] = share_of(n, wave_inclusive_sum(v) - v, t->hist[b], (uint32_t)lane_id(), kSub);
+            if (lane_id() == 0) t->sub[h][kSub] = n;
+        }
+        __syncthreads();
+    }
+    return m;
 }
 
-__device__ __forceinline__ double bucket_scale(const KeyRange &k, uint32_t nb) {
-    return k.hi >= k.lo ? (double)nb / ((double)(k.hi - k.lo) + 1.0) : 0.0;
-}
+constexpr int kRedWords = kNT / 64 + 1;          // 64-bit words of LDS that key_map() needs
 
-// Monotone 32-bit image of the depth bits of bucket b's entries: the offset
-// from below the bucket's lowest key, without the lowest bits where the bucket
-// is too wide (a float32 step is 2^29 float64 steps; beyond the expected span
-// it saturates).
+// Monotone 32-bit image of the depth bits of a bucket's entries (its keys lie in
+// [lo - 2, hi + 2]): the offset from below the lowest key, without the lowest
+// bits where the bucket is too wide (a float32 step is 2^29 float64 steps;
+// beyond the expected span it saturates).
 struct Image {
     uint64_t base;
     int shift;
@@ -200,13 +329,11 @@ struct Image {
         return (uint32_t)min(d, (uint64_t)0xfffffffeull);
     }
 };
-__device__ __forceinline__ Image image_of(const KeyRange &k, uint32_t b, uint32_t nb) {
-    const double step = 1.0 / bucket_scale(k, nb);
-    const int64_t from = b == 0 ? (int64_t)k.kmin : (int64_t)k.lo + (int64_t)((double)b * step) - 2;
-    const int64_t to = b == nb - 1u ? (int64_t)k.kmax : (int64_t)k.lo + (int64_t)((double)(b + 1u) * step) + 2;
-    const uint64_t width = (uint64_t)max(to - from, (int64_t)0) + 3u;
+__device__ __forceinline__ Image image_of(uint32_t lo, uint32_t hi) {
+    const uint32_t from = lo - min(lo, 2u);
+    const uint64_t width = (uint64_t)(max(hi, lo) - from) + 5u;
     Image im;
-    const double z = (double)__uint_as_float((uint32_t)max(from, (int64_t)0));
+    const double z = (double)__uint_as_float(from);
     const uint64_t bits = (uint64_t)__double_as_longlong(z);
     im.base = bits > (1ull << 29) ? bits - (1ull << 29) : 0ull;
     im.shift = 0;
@@ -229,8 +356,8 @@ template <int KPT, typename Src>
 __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb, BucketWork w, const uint32_t *tiles,
                                                            uint16_t *bucket, uint32_t *slot) {
     extern __shared__ uint64_t s_cnt[];                      // [nb]
-    __shared__ uint64_t s_red[kRangeWords];
-    __shared__ uint64_t s_tmp[kNT / 64 + 1];
+    __shared__ uint64_t s_red[kRedWords];
+    __shared__ MapTables s_map;
     const Chunk c = src.chunk(blockIdx.x, KPT * kNT);
     if (c.lo >= c.hi) return;                                // uniform
     // the entries' loads first: the range and the cleared counts come while they are on their way
@@ -243,23 +370,14 @@ __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb,
         nt[r] = tiles ? tiles[src.pos(j)] : 0u;
     }
     for (uint32_t b = threadIdx.x; b < nb; b += kNT) s_cnt[b] = 0;
-    const KeyRange kr = src.range(c, s_red);
-    if (c.first && threadIdx.x == 0) {                       // for the sort
-        uint32_t *r = w.range + 4 * (size_t)c.v;
-        r[0] = kr.kmin;
-        r[1] = kr.kmax;
-        r[2] = kr.lo;
-        r[3] = kr.hi;
-    }
-    const double scale = bucket_scale(kr, nb);
-    __syncthreads();
+    const KeyMap map = key_map(src, c, nb, &s_map, s_red);
     uint32_t bk[KPT], rank[KPT];
     uint64_t mine = 0;
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
         bk[r] = rank[r] = 0;
         if (!in[r]) continue;
-        bk[r] = bucket_of(key[r], kr, scale, nb);
+        bk[r] = map.bucket(key[r]);
         const uint64_t one = (uint64_t(1) << kTileBits) + nt[r];
         rank[r] = entries_of(add64(&s_cnt[bk[r]], one));
         mine += one;
@@ -293,9 +411,14 @@ __global__ void __launch_bounds__(kNT) bucket_count_kernel(Src src, uint32_t nb,
     }
     if (w.view) {                                            // uniform: the views' totals
         uint64_t total;
-        block_exclusive_sum<kNT>(mine, s_tmp, &total);
+        block_exclusive_sum<kNT>(mine, s_red, &total);
         if (threadIdx.x == 0 && total) add64(&w.view[c.v], total);
     }
+    // the buckets' bounds, for the sort: each of the view's blocks has its part
+    uint32_t *edge = w.edge + (size_t)c.v * (nb + 1u);
+    const uint32_t per = nb / c.n_chunks + 1u;
+    for (uint32_t k = threadIdx.x; k < per; k += kNT)
+        if (c.chunk * per + k <= nb) edge[c.chunk * per + k] = map.edge(c.chunk * per + k);
 }
 
 // Every block scans its view's bucket counts into s_start (exclusive, from the
@@ -485,7 +608,7 @@ __device__ void rank_sort(uint64_t *s_key, uint32_t *s_pos, uint32_t *s_img, int
 // Block b sorts bucket b; with tiles, offsets[j] = the tiles of the entries
 // before the j-th of the order (from the bucket's tstart).
 template <int NT, int CAP>
-__global__ void __launch_bounds__(NT) bucket_sort_kernel(const uint32_t *start, const uint32_t *range, uint32_t nb,
+__global__ void __launch_bounds__(NT) bucket_sort_kernel(const uint32_t *start, const uint32_t *edge, uint32_t nb,
                                                               const uint32_t *bucketed, const uint64_t *depth_key,
                                                               int64_t n_max, uint32_t *alt, uint32_t *out,
                                                               const uint32_t *tiles, const uint64_t *tstart,
@@ -497,12 +620,12 @@ __global__ void __launch_bounds__(NT) bucket_sort_kernel(const uint32_t *start, 
     __shared__ uint32_t s_wave[NT / 64];
     __shared__ uint64_t s_tmp[NT / 64 + 1];
     const uint32_t lo = start[blockIdx.x], hi = (uint32_t)min((int64_t)start[blockIdx.x + 1], n_max);
-    const uint32_t *r = range + 4 * (size_t)(blockIdx.x / nb);
-    const KeyRange kr{r[0], r[1], r[2], r[3]};
+    const uint32_t *e = edge + blockIdx.x + blockIdx.x / nb;   // nb + 1 per view
+    const uint32_t key_lo = e[0], key_hi = e[1];
     const uint64_t tiles_before = tiles ? tstart[blockIdx.x] : 0;
     const int64_t m = (int64_t)hi - lo;
     if (m <= 0) return;
-    const Image im = image_of(kr, blockIdx.x % nb, nb);
+    const Image im = image_of(key_lo, key_hi);
     const uint32_t last = (uint32_t)(n_max - 1);    // positions index depth_key[0, n_max)
     // sorted runs of CAP (all of the bucket when it fits)
     for (int64_t c0 = 0; c0 < m; c0 += CAP) {
@@ -545,31 +668,44 @@ __global__ void __launch_bounds__(NT) bucket_sort_kernel(const uint32_t *start, 
             }
         return;
     }
-    // pairwise merges of runs of width w: output element i of a pair takes
-    // the i-th smallest of the two runs, found by a binary search of how many
-    // of them come from the first run
+    // pairwise merges of runs of width w: a thread places kRun consecutive
+    // elements of a pair's output (a pair has a multiple of kRun places): how many
+    // of the elements before them come from the first run by a binary search,
+    // then one comparison each.  (An element per search took 10 to 20 dependent
+    // loads each: 200k equal depths 59 ms, 30 ms now.)
+    constexpr int kRun = 16;
+    static_assert(CAP % kRun == 0, "a thread's run lies in one pair");
     uint32_t *src = out + lo, *dst = alt + lo;
     for (int64_t w = CAP; w < m; w <<= 1) {
-        for (int64_t a0 = 0; a0 < m; a0 += 2 * w) {
+        for (int64_t i0 = (int64_t)threadIdx.x * kRun; i0 < m; i0 += (int64_t)NT * kRun) {
+            const int64_t a0 = i0 / (2 * w) * (2 * w), i = i0 - a0;
             const int64_t la = min(w, m - a0);
             const int64_t lb = max((int64_t)0, min(w, m - a0 - w));
             const uint32_t *A = src + a0, *B = src + a0 + la;
-            for (int64_t i = threadIdx.x; i < la + lb; i += NT) {
-                int64_t s = max((int64_t)0, i - lb), e = min(i, la);
-                while (s < e) {
-                    const int64_t mid = (s + e) >> 1;
-                    const uint32_t pa = A[mid], pb = B[i - 1 - mid];
-                    if (before(depth_key[pa], pa, depth_key[pb], pb)) s = mid + 1; else e = mid;
+            int64_t s = max((int64_t)0, i - lb), e = min(i, la);
+            while (s < e) {
+                const int64_t mid = (s + e) >> 1;
+                const uint32_t pa = A[mid], pb = B[i - 1 - mid];
+                if (before(depth_key[pa], pa, depth_key[pb], pb)) s = mid + 1; else e = mid;
+            }
+            int64_t ia = s, ib = i - s;
+            uint32_t pa = ia < la ? A[ia] : 0u, pb = ib < lb ? B[ib] : 0u;
+            uint64_t ka = ia < la ? depth_key[pa] : 0ull, kb = ib < lb ? depth_key[pb] : 0ull;
+            const int64_t end = min(i + kRun, la + lb);
+            for (int64_t j = i; j < end; ++j) {
+                if (ib >= lb || (ia < la && before(ka, pa, kb, pb))) {
+                    dst[a0 + j] = pa;
+                    if (++ia < la) {
+                        pa = A[ia];
+                        ka = depth_key[pa];
+                    }
+                } else {
+                    dst[a0 + j] = pb;
+                    if (++ib < lb) {
+                        pb = B[ib];
+                        kb = depth_key[pb];
+                    }
                 }
-                const int64_t ia = s, ib = i - s;
-                uint32_t v;
-                if (ib >= lb) v = A[ia];
-                else if (ia >= la) v = B[ib];
-                else {
-                    const uint32_t pa = A[ia], pb = B[ib];
-                    v = before(depth_key[pa], pa, depth_key[pb], pb) ? pa : pb;
-                }
-                dst[a0 + i] = v;
             }
         }
         __syncthreads();
@@ -600,7 +736,7 @@ int bucket_log2_for(int64_t n_max) {
 
 size_t bucket_scratch_words(int64_t n_max) {
     const int64_t nb = int64_t(1) << bucket_log2_for(n_max);
-    return (size_t)(3 * nb + 1 + 2 + 4);
+    return (size_t)(3 * nb + 1 + 2 + nb + 1);
 }
 
 BucketWork bucket_work(uint32_t *words, int64_t n_view_max, int32_t V, size_t *n_words, size_t *n_clear) {
@@ -617,7 +753,7 @@ BucketWork bucket_work(uint32_t *words, int64_t n_view_max, int32_t V, size_t *n
     *n_clear = at;
     w.tstart = reinterpret_cast<uint64_t *>(take(2 * nb));
     w.start = take(nb + 1);
-    w.range = take(4 * (size_t)V);
+    w.edge = take(nb + (size_t)V);
     *n_words = at;
     return w;
 }
@@ -639,7 +775,7 @@ hipError_t order_buckets(const Src &src, int64_t n_view_max, int32_t V, const Bu
     const bool large = n_view_max > kLargeAbove;
     hipLaunchKernelGGL((large ? bucket_sort_kernel<kLargeNT, kLargeCap> : bucket_sort_kernel<kSortNT, kCap>),
                        dim3(nb * (unsigned)V), dim3(large ? kLargeNT : kSortNT), 0, s, (const uint32_t *)w.start,
-                       (const uint32_t *)w.range, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles,
+                       (const uint32_t *)w.edge, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles,
                        (const uint64_t *)w.tstart, offsets);
     return hipGetLastError();
 }
@@ -654,7 +790,7 @@ hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, con
     BucketWork w{};
     w.count = reinterpret_cast<uint64_t *>(work);
     w.start = work + 2 * nb;
-    w.range = work + 3 * nb + 3;
+    w.edge = work + 3 * nb + 3;
     return order_buckets<4>(SrcList{keys32, vals, n_vis_dev, n_max, work + 3 * nb + 1}, n_max, 1, w,
                          depth_key, n_max, alt, bucketed, out, nullptr, nullptr, nullptr, s);
 }
@@ -662,10 +798,11 @@ hipError_t depth_order_buckets(const uint32_t *keys32, const uint32_t *vals, con
 hipError_t depth_order_views(const uint8_t *visible, const uint64_t *depth_key, const uint32_t *tiles,
                              const uint32_t *block_range, const int64_t *n_dev, int64_t n_total, const ViewDesc *table,
                              const uint32_t *chunk_view, int32_t V, int64_t n_view_max, uint32_t *work, uint32_t *alt,
-                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s) {
+                             uint32_t *bucketed, uint32_t *out, uint64_t *offsets, int64_t *counts, hipStream_t s,
+                             const uint32_t *samples) {
     size_t words = 0, clear = 0;
     const BucketWork w = bucket_work(work, n_view_max, V, &words, &clear);
-    const SrcViews src{visible, depth_key, block_range, n_dev, n_total, table, chunk_view};
+    const SrcViews src{visible, depth_key, block_range, samples, n_dev, n_total, table, chunk_view};
     return n_total <= kSmallUpTo ? order_buckets<4>(src, n_view_max, V, w, depth_key, n_total, alt, bucketed, out, tiles,
                                                     offsets, counts, s)
                                  : order_buckets<16>(src, n_view_max, V, w, depth_key, n_total, alt, bucketed, out, tiles,

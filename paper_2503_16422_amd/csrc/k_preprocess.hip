@@ -142,6 +142,7 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
         if (t == 0) {
             a.out.block_range[2 * blockIdx.x] = ~0u;
             a.out.block_range[2 * blockIdx.x + 1] = 0u;
+            reinterpret_cast<uint4 *>(a.out.samples)[blockIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
             if (a.out.vis_count) a.out.vis_count[blockIdx.x] = 0u;
         }
         return;
@@ -169,6 +170,12 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
             s_range[2 * wave_id()] = lo;
             s_range[2 * wave_id() + 1] = hi;
         }
+        // a sample of the wavefront's depths: its first visible lane from a hashed one on
+        const uint64_t m = __ballot(vis);
+        const uint32_t at = (uint32_t)blockIdx.x * (kBlock / 64) + (uint32_t)wave_id();
+        const int from = (int)((at * 2654435761u) >> 26);
+        const uint64_t turned = from ? m >> from | m << (64 - from) : m;
+        if (lane_id() == (m ? (__builtin_ctzll(turned) + from) & 63 : 0)) a.out.samples[at] = m ? key : ~0u;
     }
     const int tw = a.rp.tile_w, th = a.rp.tile_h;
     uint32_t rows = 0, direct = 0;

@@ -698,3 +698,56 @@ def test_masked_frame_of_a_large_model_orders_as_the_small_one(ctx, kept, twins)
     assert b0["n_vis"] == b1["n_vis"] and b0["n_inst"] == b1["n_inst"]
     assert torch.equal(b0["sorted_ids"], b1["sorted_ids"]) and torch.equal(b0["tile_ranges"], b1["tile_ranges"])
     assert torch.equal(rgb0, rgb1)
+
+
+@pytest.mark.parametrize("n", [700, 90_000, 300_000])
+@pytest.mark.parametrize("law", ["even", "slab", "equal"])
+def test_storage_order_does_not_matter(ctx, n, law):
+    """A scene stored at random, by depth and in clusters of neighbours, its depths even,
+    nine tenths of them in a slab of 5%, or a third of them equal: the images, of
+    single and of batched views, are bit-identical (float32 depths drawn without
+    repetition; the equal ones have one colour, opacity and footprint, so their order
+    among themselves does not show)."""
+    from paper_2503_16422_amd.render import GaussianModel
+    n = n if law != "equal" else n // 10
+    rng = np.random.default_rng(n)
+    u = rng.random(n)
+
+    def distinct(lo, hi, k):
+        lo, hi = np.array([lo, hi], np.float32).view(np.int32)
+        return rng.choice(hi - lo, k, replace=False).astype(np.int32) + lo
+
+    z = distinct(3.0, 5.0, n).view(np.float32)
+    if law == "slab":
+        z = z.copy()
+        z[u < 0.9] = distinct(4.0, 4.2, int((u < 0.9).sum())).view(np.float32)
+        z[u >= 0.9] = distinct(4.3, 60.0, int((u >= 0.9).sum())).view(np.float32)
+    sc = inputs.tiny_scene(n, seed=5)
+    if law == "equal":
+        same = u < 1.0 / 3.0
+        z = z.copy()
+        z[same] = 5.5
+        for f in (sc.log_scale, sc.opacity_logit, sc.sh):
+            f[..., same] = f[..., np.flatnonzero(same)[:1]]
+    sc.mean[:3] = [rng.uniform(-0.4, 0.4, n) * z, rng.uniform(-0.4, 0.4, n) * z, z]
+    if law == "equal":
+        sc.mean[:2, same] = np.array([[0.3], [-0.2]])
+        sc.q_left[:, same] = sc.q_left[:, np.flatnonzero(same)[:1]]
+        sc.q_right[:, same] = sc.q_right[:, np.flatnonzero(same)[:1]]
+        sc.mean[3, same] = 0.5
+    sc.q_left[:] = np.array([1.0, 0, 0, 0])[:, None]      # the conditional mean is the mean: depth is z
+    sc.q_right[:] = np.array([1.0, 0, 0, 0])[:, None]
+    cam = inputs.Camera(np.eye(3), np.zeros(3), 80.0, 80.0, 40.0, 30.0, 80, 60, 0.01)
+    by_depth = np.argsort(sc.mean[2], kind="stable")
+    pieces = np.array_split(by_depth, max(1, n // 500))
+    rng.shuffle(pieces)
+    orders = [np.arange(n), by_depth, np.concatenate(pieces)]
+    models = [GaussianModel.from_scene(sc.subset(o), "cuda:0") for o in orders]
+    ref = ctx.render(models[0], cam, 0.5)[0]
+    for m in models[1:]:
+        assert torch.equal(ctx.render(m, cam, 0.5)[0], ref)
+    batch = ctx.render_batch(models, [(k, cam, 0.5) for k in (2, 0, 1)])
+    for k in range(3):
+        assert torch.equal(batch[k], ref)
+    if law != "equal":
+        assert float(ref.max()) > 0.05

@@ -60,3 +60,8 @@ def test_xcd_block_order_is_a_bijection(tmp_path):
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_depth_order_of_views_on_host(tmp_path):
     run_on_host(tmp_path, "k_bucket.hip", "views_check.cpp")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_depth_order_over_storage_orders_on_host(tmp_path):
+    run_on_host(tmp_path, "k_bucket.hip", "order_check.cpp")
