@@ -149,13 +149,15 @@ void release(Buf &b) {
 }
 
 constexpr int32_t kDefaultPpt = 2;
-// Largest processed count of a view ordered by buckets.  Above it most buckets
-// outgrow a workgroup's LDS and the radix sort is the faster (unfiltered frame
-// of 3M).  With a device count (a mask) the bound is the model's size, of which
-// a mask keeps a fraction: a masked frame of 3M Gaussians, 0.8M of them
-// processed, takes 645 us with the radix sort and 611 with buckets.
+// Largest processed count of a view ordered by buckets, of which there are at most
+// 4096: a bucket's ranking grows with its square.  Order of one view, all visible,
+// by buckets and by the radix sort: 200k 45 and 74 us, 500k 77 and 86, 700k 106 and
+// 100, 1M 156 and 115, 1.5M 280 and 153; four batched views of 300k 104 and 181, of
+// 800k 325 and 358.  Up to the bound more than 4096 equal depths are in order, too,
+// which the radix path reports as an error.  With a device count (a mask) the bound
+// is the model's size, since a mask may keep all of it (3M, 27% kept: 128 and 153
+// us; 60%: 367 and 186; all: 760 and 239).
 constexpr int64_t kBucketMaxN = int64_t(1) << 20;
-constexpr int64_t kBucketMaxMasked = int64_t(1) << 22;
 
 // Several views of one forward pass: device copies of their descriptions and of
 // the view of each chunk of entries, the largest processed count and their sum
@@ -860,7 +862,7 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     HIP_TRY(ensure(S->offsets, sizeof(uint64_t) * n_max));
     // views of not too many processed Gaussians: depth order and offsets by buckets (three launches)
     const int64_t n_view_max = vt.views ? vt.max_n : n_max;
-    const bool by_buckets = n_max > 0 && n_view_max <= (n_dev ? kBucketMaxMasked : kBucketMaxN) &&
+    const bool by_buckets = n_max > 0 && n_view_max <= kBucketMaxN &&
                             n_view_max * tiles_per_view < (int64_t(1) << kBucketTileBits);
     size_t bucket_words = 0, bucket_clear = 0;
     if (by_buckets) {

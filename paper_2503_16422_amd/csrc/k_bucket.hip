@@ -48,15 +48,12 @@ constexpr int kNT = 256;
 // 16 views of 225k: 134 -> 67 us).
 constexpr int64_t kSmallUpTo = int64_t(1) << 18;
 static_assert(kViewChunk == 16 * kNT, "a workgroup's entries belong to one view");
-// A sorting workgroup (NT threads, CAP positions in LDS at once) is a chain of
-// loads (start, position, depth) and a short ranking: what counts is that all
-// of them (one per bucket, 4096 for a frame) are resident at once, 16 on a CU:
-// 128 threads and under 10 KB of LDS.  Above 2^20 entries a bucket holds
-// several hundred and wants the larger form, or it would be sorted in pieces
-// and merged (masked frame of 3M, 0.66M visible: 82 -> 65 us).
+// A sorting workgroup is a chain of loads (start, position, depth) and a short
+// ranking: what counts is that all of them (one per bucket, 4096 for a frame) are
+// resident at once, 16 on a CU: 128 threads and under 10 KB of LDS.  (256 threads
+// and 1024 positions: depth order of 200k 50 us against 45, 1M 152 against 156,
+// four views of 300k 136 against 104, of 800k 348 against 325.)
 constexpr int kSortNT = 128, kCap = 384;
-constexpr int kLargeNT = 256, kLargeCap = 1024;
-constexpr int64_t kLargeAbove = int64_t(1) << 20;
 
 __device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_max) {
     return n_dev ? min(*n_dev, n_max) : n_max;
@@ -772,9 +769,7 @@ hipError_t order_buckets(const Src &src, int64_t n_view_max, int32_t V, const Bu
     hipLaunchKernelGGL((bucket_scatter_kernel<KPT, Src>), dim3((unsigned)chunks), dim3(kNT), sizeof(uint32_t) * nb, s, src, nb,
                        (int)V, w, reinterpret_cast<const uint16_t *>(out), (const uint32_t *)alt, bucketed, n_max,
                        tiles != nullptr, counts);
-    const bool large = n_view_max > kLargeAbove;
-    hipLaunchKernelGGL((large ? bucket_sort_kernel<kLargeNT, kLargeCap> : bucket_sort_kernel<kSortNT, kCap>),
-                       dim3(nb * (unsigned)V), dim3(large ? kLargeNT : kSortNT), 0, s, (const uint32_t *)w.start,
+    hipLaunchKernelGGL((bucket_sort_kernel<kSortNT, kCap>), dim3(nb * (unsigned)V), dim3(kSortNT), 0, s, (const uint32_t *)w.start,
                        (const uint32_t *)w.edge, nb, (const uint32_t *)bucketed, depth_key, n_max, alt, out, tiles,
                        (const uint64_t *)w.tstart, offsets);
     return hipGetLastError();
