@@ -329,7 +329,7 @@ FDGS_API fdgs_status fdgs_state_binning(fdgs_ctx *ctx, fdgs_state *state, fdgs_b
  * (5) Batched forward for many views across scenes of uneven size (a
  * multi-view workload such as rendering every (camera, timestamp) of several
  * dynamic scenes).  The views are processed in launches of views_per_launch
- * views (0: all at once): each launch runs every stage once over the
+ * views (0: all at once; at most 1024): each launch runs every stage once over the
  * concatenated (view, Gaussian) space, bins with (view, tile) keys and
  * blends all views' tiles in one compositor launch.  Results equal
  * fdgs_render_forward of each view (no state is kept).

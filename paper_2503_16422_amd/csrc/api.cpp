@@ -158,7 +158,6 @@ constexpr int32_t kDefaultPpt = 2;
 // is the model's size, since a mask may keep all of it (3M, 27% kept: 128 and 153
 // us; 60%: 367 and 186; all: 760 and 239).
 constexpr int64_t kBucketMaxN = int64_t(1) << 20;
-
 // Several views of one forward pass: device copies of their descriptions and of
 // the view of each chunk of entries, the largest processed count and their sum
 // (without the padding of the chunks).
@@ -1176,6 +1175,15 @@ fdgs_status run_side_views(fdgs_ctx *ctx, const fdgs_model *model, const SidePas
     return fail(FDGS_ERR_HIP, "fdgs_render: out of host memory");
 }
 
+// Views per launch of a batch: as asked, but no more than share one usefully.  A
+// view takes whole chunks of entries and the buckets that the largest one needs,
+// each a workgroup: tens of thousands of tiny views in one launch would take
+// gigabytes of padding, and beside a large one more workgroups than a grid holds.
+constexpr int32_t kBatchMostViews = 1024;
+int32_t views_in_launch(int32_t asked, int32_t n_views) {
+    return std::min({asked > 0 ? asked : n_views, n_views, kBatchMostViews});
+}
+
 // Enqueue every launch of a batch (no graph handling).
 fdgs_status enqueue_batch(fdgs_ctx *ctx, const fdgs_model *scenes, const fdgs_view *views, int32_t n_views,
                           const fdgs_render_cfg *cfg, int32_t per_launch, bool upload, float *out_rgb,
@@ -1263,7 +1271,7 @@ fdgs_status fdgs_render_batch(fdgs_ctx *ctx, const fdgs_model *scenes, int32_t n
     if (views_per_launch < 0) return fail(FDGS_ERR_INVALID_ARG, "%s: views_per_launch < 0", fn);
     if (use_graph && cfg->instance_capacity <= 0)
         return fail(FDGS_ERR_INVALID_ARG, "%s: use_graph needs a fixed instance_capacity", fn);
-    const int32_t per = views_per_launch ? std::min(views_per_launch, n_views) : n_views;
+    const int32_t per = views_in_launch(views_per_launch, n_views);
     HIP_TRY(hipSetDevice(ctx->device));
     if (!use_graph) {
         drop_graph(ctx);
@@ -1318,7 +1326,7 @@ fdgs_status fdgs_autotune(fdgs_ctx *ctx, const fdgs_model *scenes, int32_t n_sce
     if (fdgs_status st = check_batch(scenes, n_scenes, views, n_views, fn)) return st;
     if (fdgs_status st = check_cfg(inout_cfg, fn)) return st;
     if (repeats < 1) repeats = 1;
-    const int32_t per = views_per_launch > 0 ? std::min(views_per_launch, n_views) : n_views;
+    const int32_t per = views_in_launch(views_per_launch, n_views);
     HIP_TRY(hipSetDevice(ctx->device));
     drop_graph(ctx);
     const size_t img_bytes = sizeof(float) * 3ull * views[0].cam.width * views[0].cam.height * n_views;
