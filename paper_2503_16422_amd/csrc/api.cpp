@@ -186,6 +186,7 @@ struct fdgs_state {
     fdgs_ctx *owner = nullptr;
     bool has_forward = false;
     bool has_g2d = false;   // a backward's first phase ran since the last forward
+    bool g2d_wide = true;   // the form it left its sums in
     bool ordered = false;   // sched holds the last forward's tiles longest list first
     // per processed Gaussian
     Buf rec, depth_key, rect, tiles, visible, vis_pos, order_k, order_v, order_k2, order_v2, offsets;
@@ -1429,9 +1430,24 @@ fdgs_status check_grads(const fdgs_state *S, const fdgs_grads *grads, const char
 fdgs_status enqueue_backward_2d(fdgs_ctx *ctx, fdgs_state *S, const float *dL_drgb, hipStream_t stream) {
     if (stream != nullptr) S->beyond_null_stream = true;
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(ensure(S->g2d, sizeof(double) * kG2dStride * std::max<int64_t>(S->n_max, 1)));
+    // float64 lines, or float32 (28% of their memory) where those do not fit; a state that found
+    // no room for them does not ask again while its block is large enough for the small form
+    const int64_t n_g2d = std::max<int64_t>(S->n_max, 1);
+    const size_t lines = G2d::bytes(n_g2d, true), small = G2d::bytes(n_g2d, false);
+    S->g2d_wide = S->g2d_wide || S->g2d.cap < small || S->g2d.cap >= lines;
+    if (S->g2d_wide) {
+        const hipError_t e = ensure(S->g2d, lines);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            S->g2d_wide = false;
+        } else {
+            HIP_TRY(e);
+        }
+    }
+    if (!S->g2d_wide) HIP_TRY(ensure(S->g2d, small));
+    const G2d g2d{S->g2d.p, S->g2d_wide};
     StageTimer tm(ctx, FDGS_STAGE_BWD_COMPOSITE, stream);
-    HIP_TRY(launch_clear_g2d(S->vis_list, S->counts.as<int64_t>(), S->n_max, S->g2d.as<double>(), stream));
+    HIP_TRY(launch_clear_g2d(S->vis_list, S->counts.as<int64_t>(), S->n_max, g2d, stream));
     // the adjoint takes the tiles longest list first: the forward's order when it
     // made one, else one made here
     const int32_t n_tiles = S->rp.tiles_x * S->rp.tiles_y;
@@ -1442,7 +1458,7 @@ fdgs_status enqueue_backward_2d(fdgs_ctx *ctx, fdgs_state *S, const float *dL_dr
     }
     HIP_TRY(launch_composite_backward(S->rp, S->W, S->H, S->batch, S->ppt, S->ranges.as<uint32_t>(), S->sorted_ids,
                                       S->rec.as<Rec2D>(), S->T_final.as<float>(), S->n_contrib.as<uint32_t>(),
-                                      dL_drgb, S->g2d.as<double>(), S->n_max, S->sched.as<uint32_t>(), stream));
+                                      dL_drgb, g2d, S->n_max, S->sched.as<uint32_t>(), stream));
     S->has_g2d = true;
     return FDGS_OK;
 }
@@ -1454,7 +1470,7 @@ fdgs_status enqueue_backward_params(fdgs_ctx *ctx, fdgs_state *S, const fdgs_gra
     StageTimer tm(ctx, FDGS_STAGE_BWD_PREPROCESS, stream);
     const int64_t *n_proc_dev = S->idx ? S->n_idx_dev : nullptr;
     HIP_TRY(launch_preprocess_backward(kmodel(&S->model), S->idx, n_proc_dev, S->n_max, S->cam, S->t, S->rp,
-                                       S->vis_list, S->counts.as<int64_t>(), S->g2d.as<double>(), *grads, stream));
+                                       S->vis_list, S->counts.as<int64_t>(), G2d{S->g2d.p, S->g2d_wide}, *grads, stream));
     return FDGS_OK;
 }
 

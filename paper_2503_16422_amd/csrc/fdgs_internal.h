@@ -182,13 +182,21 @@ hipError_t measure_peaks(float *sink, double *out, hipStream_t s);
 // out[0..2] = popcounts of a, b and a & b over the first n bits (device int64[3]).
 hipError_t launch_mask_overlap(const uint32_t *a, const uint32_t *b, int64_t n, int64_t *out, hipStream_t s);
 
-// Backward.  Doubles per Gaussian of the 2D gradients g2d: nine values in a 128-byte line of their own.
-constexpr int kG2dStride = 16;
-hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, double *g2d, hipStream_t s);
+// Backward.  The nine 2D gradients of each Gaussian: float64 in a 128-byte line of its own (kG2dStride values),
+// or, where those do not fit into memory, float32 side by side.
+constexpr int kG2dStride = 16, kG2dVals = 9;
+struct G2d {
+    void *p;
+    bool wide;
+    __host__ __device__ double *line(int64_t i) const { return static_cast<double *>(p) + i * kG2dStride; }
+    __host__ __device__ float *narrow(int64_t i) const { return static_cast<float *>(p) + i * kG2dVals; }
+    static size_t bytes(int64_t n, bool wide) { return wide ? sizeof(double) * kG2dStride * n : sizeof(float) * kG2dVals * n; }
+};
+hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, G2d g2d, hipStream_t s);
 hipError_t launch_composite_backward(const RenderParams &rp, int32_t W, int32_t H, int32_t batch, int32_t ppt,
                                      const uint32_t *ranges, const uint32_t *ids, const Rec2D *rec,
                                      const float *T_final, const uint32_t *n_contrib,
-                                     const float *dL_drgb, double *g2d, int64_t n_proc_max,
+                                     const float *dL_drgb, G2d g2d, int64_t n_proc_max,
                                      const uint32_t *order, hipStream_t s);
 // order[0 .. n_items): the items of ranges sorted by list length, longest first
 // (the order of the compositors' longest-first schedule).
@@ -196,7 +204,7 @@ hipError_t launch_tile_order(const uint32_t *ranges, int32_t n_items, uint32_t *
 hipError_t launch_preprocess_backward(const KModel &m, const uint32_t *idx, const int64_t *n_dev,
                                       int64_t n_max, const KCam &cam, double t,
                                       const RenderParams &rp, const uint32_t *vis_list,
-                                      const int64_t *n_vis_dev, const double *g2d, const fdgs_grads &grads,
+                                      const int64_t *n_vis_dev, G2d g2d, const fdgs_grads &grads,
                                       hipStream_t s);
 
 // Pruning score helpers (k_prune.hip).

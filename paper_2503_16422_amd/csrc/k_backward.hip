@@ -25,7 +25,7 @@ struct BArgs {
     double dilation;
     const uint32_t *vis_list;   // processed positions of the visible Gaussians, ascending
     const int64_t *n_vis_dev;   // their count (device)
-    const double *g2d;
+    G2d g2d;
     fdgs_grads grads;
 };
 
@@ -43,12 +43,17 @@ __global__ void __launch_bounds__(kBlock) preprocess_bwd_kernel(BArgs a) {
     if (g >= n) return;
     Gauss4 G;
     if (!load_gaussian(a.m, g, G)) return;
-    const double2 *gi = reinterpret_cast<const double2 *>(a.g2d + i * kG2dStride);
-    const double2 g01 = gi[0], g23 = gi[1], g45 = gi[2], g67 = gi[3];
-    const double du = g01.x, dv = g01.y;
-    const double dca = g23.x, dcb = g23.y, dcc = g45.x;
-    const double dop = g45.y;
-    const double drgb[3] = {g67.x, g67.y, gi[4].x};
+    double du, dv, dca, dcb, dcc, dop, drgb[3];
+    if (a.g2d.wide) {                                        // uniform
+        const double2 *gi = reinterpret_cast<const double2 *>(a.g2d.line(i));
+        const double2 g01 = gi[0], g23 = gi[1], g45 = gi[2], g67 = gi[3];
+        du = g01.x, dv = g01.y, dca = g23.x, dcb = g23.y, dcc = g45.x, dop = g45.y;
+        drgb[0] = g67.x, drgb[1] = g67.y, drgb[2] = gi[4].x;
+    } else {
+        const float *gi = a.g2d.narrow(i);
+        du = gi[0], dv = gi[1], dca = gi[2], dcb = gi[3], dcc = gi[4], dop = gi[5];
+        drgb[0] = gi[6], drgb[1] = gi[7], drgb[2] = gi[8];
+    }
 
     // ---- forward recompute (float64) ----
     const double nl = sqrt(G.ql[0] * G.ql[0] + G.ql[1] * G.ql[1] + G.ql[2] * G.ql[2] + G.ql[3] * G.ql[3]);
@@ -328,7 +333,7 @@ __global__ void __launch_bounds__(kBlock) preprocess_bwd_kernel(BArgs a) {
 hipError_t launch_preprocess_backward(const KModel &m, const uint32_t *idx, const int64_t *n_dev,
                                       int64_t n_max, const KCam &cam, double t,
                                       const RenderParams &rp, const uint32_t *vis_list,
-                                      const int64_t *n_vis_dev, const double *g2d, const fdgs_grads &grads,
+                                      const int64_t *n_vis_dev, G2d g2d, const fdgs_grads &grads,
                                       hipStream_t s) {
     if (n_max == 0) return hipSuccess;
     BArgs a{m, idx, n_dev, n_max, cam, t, (double)rp.dilation, vis_list, n_vis_dev, g2d, grads};

@@ -22,7 +22,7 @@ struct BwdArgs {
     const float *T_final;
     const uint32_t *n_contrib;
     const float *dL;
-    double *g2d;       // [n_proc][kG2dStride]: du, dv, d conic a, b, c, d opacity, d rgb
+    G2d g2d;           // per entry: du, dv, d conic a, b, c, d opacity, d rgb
     const uint32_t *order;   // tiles longest list first (workgroup b takes tile order[b]), or NULL: raster order
 };
 
@@ -285,21 +285,24 @@ __global__ void __launch_bounds__(TW *TH / PPT) composite_bwd_kernel(BwdArgs a) 
                 else if (j == 5) out = m / s_rec[3 * k + 2].z;                    // d opacity
                 else out = (j == 3 ? -1.0f : -0.5f) * m;                          // d conic a, b, c
             }
-            if (out != 0.0f)
-                atomicAdd(a.g2d + (int64_t)__float_as_uint(s_rec[3 * k + 2].w) * kG2dStride + j, (double)out);
+            if (out == 0.0f) continue;
+            const int64_t id = (int64_t)__float_as_uint(s_rec[3 * k + 2].w);
+            if (a.g2d.wide) atomicAdd(a.g2d.line(id) + j, (double)out);   // uniform
+            else atomicAdd(a.g2d.narrow(id) + j, out);
         }
         __syncthreads();
         for (int i = threadIdx.x; i < cnt * kVals; i += NT) s_acc[i] = 0.0f;
     }
 }
 
-// Zeroes the visible Gaussians' lines of g2d, the only ones the adjoint adds to and reads.
+// Zeroes the visible Gaussians' values of g2d, the only ones the adjoint adds to and reads: PER
+// pieces of type T per Gaussian.
+template <typename T, int PER>
 __global__ void __launch_bounds__(256) clear_g2d_kernel(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max,
-                                                        double2 *g2d) {
-    constexpr int kVec = kG2dStride / 2;
-    const int64_t n = min(*n_vis_dev, n_max) * kVec;
+                                                        T *g2d) {
+    const int64_t n = min(*n_vis_dev, n_max) * PER;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        g2d[(int64_t)vis_list[i / kVec] * kVec + i % kVec] = make_double2(0.0, 0.0);
+        g2d[(int64_t)vis_list[i / PER] * PER + i % PER] = T{};
 }
 
 // Pixels per thread in the adjoint: 1 for 8x8 tiles, else 4 when the forward
@@ -324,7 +327,7 @@ void launch_bwd(const BwdLaunch &l, int n_tiles, hipStream_t s) {
 hipError_t launch_composite_backward(const RenderParams &rp, int32_t W, int32_t H, int32_t batch, int32_t ppt,
                                      const uint32_t *ranges, const uint32_t *ids, const Rec2D *rec,
                                      const float *T_final, const uint32_t *n_contrib,
-                                     const float *dL_drgb, double *g2d, int64_t /*n_proc_max*/,
+                                     const float *dL_drgb, G2d g2d, int64_t /*n_proc_max*/,
                                      const uint32_t *order, hipStream_t s) {
     BwdLaunch l{BwdArgs{rp, W, H, ranges, ids, rec, T_final, n_contrib, dL_drgb, g2d, order}, ppt};
     const int n_tiles = rp.tiles_x * rp.tiles_y;
@@ -332,11 +335,15 @@ hipError_t launch_composite_backward(const RenderParams &rp, int32_t W, int32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, double *g2d, hipStream_t s) {
+hipError_t launch_clear_g2d(const uint32_t *vis_list, const int64_t *n_vis_dev, int64_t n_max, G2d g2d, hipStream_t s) {
     if (n_max == 0) return hipSuccess;
-    const int64_t threads = n_max * (kG2dStride / 2);
-    hipLaunchKernelGGL(clear_g2d_kernel, dim3((unsigned)std::min<int64_t>((threads + 255) / 256, 2048)), dim3(256), 0, s,
-                       vis_list, n_vis_dev, n_max, reinterpret_cast<double2 *>(g2d));
+    const dim3 grid((unsigned)std::min<int64_t>((n_max * (kG2dStride / 2) + 255) / 256, 2048));
+    if (g2d.wide)
+        hipLaunchKernelGGL((clear_g2d_kernel<double2, kG2dStride / 2>), grid, dim3(256), 0, s, vis_list, n_vis_dev, n_max,
+                           static_cast<double2 *>(g2d.p));
+    else
+        hipLaunchKernelGGL((clear_g2d_kernel<float, kG2dVals>), grid, dim3(256), 0, s, vis_list, n_vis_dev, n_max,
+                           static_cast<float *>(g2d.p));
     return hipGetLastError();
 }
 
