@@ -1702,8 +1702,15 @@ fdgs_status fdgs_sh_kmeans(fdgs_ctx *ctx, const fdgs_model *model, const uint32_
         return fail(FDGS_ERR_INVALID_ARG, "%s: codebook must be 16-byte aligned", fn);
     if (model->n == 0) return FDGS_OK;
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(ensure(ctx->vq_scratch, vq_scratch_bytes(model->n, k)));
-    HIP_TRY(vq_kmeans(model->sh, model->n, init_index, k, iterations, codebook, assignment, ctx->vq_scratch.p,
+    bool lean = false;   // no room for the screening's arrays: the search alone, in a tenth of the memory
+    hipError_t e = ensure(ctx->vq_scratch, vq_scratch_bytes(model->n, k, lean));
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        lean = true;
+        e = ensure(ctx->vq_scratch, vq_scratch_bytes(model->n, k, lean));
+    }
+    HIP_TRY(e);
+    HIP_TRY(vq_kmeans(model->sh, model->n, init_index, k, iterations, codebook, assignment, ctx->vq_scratch.p, lean,
                       stream));
     return FDGS_OK;
 }

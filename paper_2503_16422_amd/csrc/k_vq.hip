@@ -381,19 +381,21 @@ __global__ void __launch_bounds__(kNT) vq_resolve_kernel(const float *in1, const
 // the entries per workgroup (one wavefront; the entry is the same for every
 // lane, so its components come through the scalar cache), 96 operations per
 // pair.  (distance bits, entry) packed in 64 bits order as distance, then
-// entry; a NaN or an infinity never beats the start value.
+// entry; a NaN or an infinity never beats the start value.  Without a list every
+// Gaussian is open, at the place of its number.
 constexpr int kExactEntries = 64;    // entries per workgroup
 constexpr int kExactGroups = 128;    // workgroups along the list (each strides over it)
+constexpr int kLeanGroups = 4096;    // the same without a list
 template <bool ROWS>
 __global__ void __launch_bounds__(64) vq_exact_kernel(const float *__restrict__ x, int64_t n,
                                                       const float *__restrict__ code, int64_t k,
                                                       const uint32_t *__restrict__ open_list,
                                                       const uint32_t *__restrict__ n_open, unsigned long long *best) {
-    const int64_t cnt = *n_open;
+    const int64_t cnt = open_list ? (int64_t)*n_open : n;
     const int64_t j0 = (int64_t)blockIdx.x * kExactEntries, j1 = min(j0 + kExactEntries, k);
     for (int64_t g = blockIdx.y; g * 64 < cnt; g += gridDim.y) {
         const int64_t slot = g * 64 + threadIdx.x;
-        const int64_t i = open_list[min(slot, cnt - 1)];
+        const int64_t i = open_list ? (int64_t)open_list[min(slot, cnt - 1)] : min(slot, n - 1);
         float v[kD];
 #pragma unroll
         for (int d = 0; d < kD; ++d) v[d] = component<ROWS>(x, n, i, d);
@@ -415,6 +417,14 @@ __global__ void __launch_bounds__(64) vq_exact_kernel(const float *__restrict__ 
         if (slot < cnt && low < INFINITY)
             atomicMin(&best[slot], ((unsigned long long)__float_as_uint(low) << 32) | lj);
     }
+}
+
+// Every Gaussian open, without a screening.
+__global__ void __launch_bounds__(kNT) vq_open_all_kernel(int64_t n, uint32_t *assign, unsigned long long *best) {
+    const int64_t i = (int64_t)blockIdx.x * kNT + threadIdx.x;
+    if (i >= n) return;
+    best[i] = (unsigned long long)__float_as_uint(INFINITY) << 32;
+    assign[i] = kOpen | (uint32_t)i;
 }
 
 // The open Gaussians' assignments filled in; with keys, also the (cluster,
@@ -483,7 +493,10 @@ inline Sweep sweep_of(int64_t n, int64_t k) {
     return sw;
 }
 
+// lean: only what the update's sort needs (16 bytes per Gaussian); the search's
+// 64-bit results then lie in its second buffers.
 struct VqScratch {
+    bool lean;
     uint32_t *keys, *vals, *keys2, *vals2, *ranges, *open_list, *n_open, *pick;
     unsigned long long *best;
     float *rows, *top1, *top2, *x_norm2, *c_norm2, *start;
@@ -492,8 +505,9 @@ struct VqScratch {
     size_t bytes;
 };
 
-VqScratch vq_layout(void *scratch, int64_t n, int64_t k) {
-    VqScratch v;
+VqScratch vq_layout(void *scratch, int64_t n, int64_t k, bool lean) {
+    VqScratch v{};
+    v.lean = lean;
     uintptr_t at = reinterpret_cast<uintptr_t>(scratch);
     const uintptr_t base = at;
     auto take = [&](size_t bytes) {
@@ -505,9 +519,19 @@ VqScratch vq_layout(void *scratch, int64_t n, int64_t k) {
     const Sweep sw = sweep_of(n, k);
     const int64_t n_tiles = sw.n_tiles;
     const int64_t sn = n * ((n_tiles + sw.per - 1) / sw.per + 1);    // places a block can have
-    for (uint32_t **p : {&v.keys, &v.vals, &v.keys2, &v.vals2, &v.open_list})
+    for (uint32_t **p : {&v.keys, &v.vals})
         *p = static_cast<uint32_t *>(take(sizeof(uint32_t) * n));
     v.ranges = static_cast<uint32_t *>(take(sizeof(uint32_t) * 2 * k));
+    if (lean) {
+        const int64_t whole = (n + 63) / 64 * 64;
+        v.best = static_cast<unsigned long long *>(take(sizeof(unsigned long long) * whole));
+        v.keys2 = reinterpret_cast<uint32_t *>(v.best);
+        v.vals2 = v.keys2 + whole;
+        v.sort = take(sort_scratch_bytes(n));
+        v.bytes = at - base + 256;
+        return v;
+    }
+    for (uint32_t **p : {&v.keys2, &v.vals2, &v.open_list}) *p = static_cast<uint32_t *>(take(sizeof(uint32_t) * n));
     v.n_open = static_cast<uint32_t *>(take(sizeof(uint32_t)));
     v.best = static_cast<unsigned long long *>(take(sizeof(unsigned long long) * n));
     v.rows = n <= kRowsUpTo ? static_cast<float *>(take(sizeof(float) * kD * n)) : nullptr;
@@ -525,16 +549,26 @@ VqScratch vq_layout(void *scratch, int64_t n, int64_t k) {
 
 }  // namespace
 
-size_t vq_scratch_bytes(int64_t n, int64_t k) { return vq_layout(nullptr, n, k).bytes; }
+size_t vq_scratch_bytes(int64_t n, int64_t k, bool lean) { return vq_layout(nullptr, n, k, lean).bytes; }
 
 hipError_t vq_kmeans(const float *sh, int64_t n, const uint32_t *init, int64_t k, int32_t iterations, float *code,
-                     uint32_t *assign, void *scratch, hipStream_t s) {
+                     uint32_t *assign, void *scratch, bool lean, hipStream_t s) {
     if (n <= 0 || k <= 0) return hipSuccess;
-    const VqScratch v = vq_layout(scratch, n, k);
+    const VqScratch v = vq_layout(scratch, n, k, lean);
     const Sweep sw = sweep_of(n, k);
     const int n_tiles = sw.n_tiles;
     const float *x = v.rows ? v.rows : sh;
     auto assign_all = [&](uint32_t *keys, uint32_t *vals) {
+        if (v.lean) {
+            hipLaunchKernelGGL(vq_open_all_kernel, dim3(blocks(n, kNT)), dim3(kNT), 0, s, n, assign, v.best);
+            hipLaunchKernelGGL(vq_exact_kernel<false>,
+                               dim3(blocks(k, kExactEntries), std::min(blocks(n, 64), (unsigned)kLeanGroups)), dim3(64), 0,
+                               s, x, n, (const float *)code, k, (const uint32_t *)nullptr, (const uint32_t *)nullptr,
+                               v.best);
+            hipLaunchKernelGGL(vq_keys_kernel, dim3(blocks(n, kNT)), dim3(kNT), 0, s, assign,
+                               (const unsigned long long *)v.best, n, keys, vals);
+            return;
+        }
         hipLaunchKernelGGL(vq_frag_kernel, dim3((unsigned)n_tiles), dim3(64), 0, s, (const float *)code, k, v.frag,
                            v.start, v.c_norm2, v.n_open);
         hipLaunchKernelGGL(vq_screen_kernel, dim3((unsigned)((sw.total() + sw.per - 1) / sw.per)),

@@ -67,3 +67,28 @@ def test_adjoint_without_room_for_float64_lines():
     for g in out[1:]:
         for k, ref in out[0].items():
             assert torch.allclose(g[k], ref, rtol=1e-4, atol=1e-5 * float(ref.abs().max()) + 1e-12), k
+
+
+def test_kmeans_without_room_for_the_screening():
+    """2^22 Gaussians want about 1 GB for the screened search; with 0.4 GB free the
+    codebook is found by the plain search (70 MB).  Codebook and assignment are the
+    same bit for bit, with a NaN and enormous coefficients among the vectors."""
+    from paper_2503_16422_amd.render import Context
+    n, kept = 1 << 22, 5000
+    model = large_model(n, kept)
+    model.sh[3, 1, 17] = float("nan")
+    model.sh[2, 0, 21:25] = 1e20
+    init = torch.from_numpy(np.random.default_rng(3).choice(kept, 70, replace=False).astype(np.int32)).cuda()
+    out = []
+    for small in (False, True):
+        ctx = Context(0)
+        with all_memory_taken_but(400 << 20) if small else contextlib.nullcontext():
+            before = torch.cuda.mem_get_info()[0]
+            code, assign = ctx.sh_kmeans(model, 70, 2, init_index=init)
+            torch.cuda.synchronize()
+            taken = before - torch.cuda.mem_get_info()[0]
+        assert (taken < 200 << 20) == small
+        out.append((code.view(torch.int32).clone(), assign.clone()))
+        ctx.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert int(out[0][1].max()) < 70
