@@ -30,12 +30,13 @@ __global__ void __launch_bounds__(kBlock) temporal_volume_kernel(KModel m, const
     uint32_t key = 0u;
     if (load_gaussian(m, i, G)) {
         const double s44 = sigma44_of(G);
-        const double i0 = -1.0 / (2.0 * s44), i1 = 1.0 / s44, i2 = 1.0 / (s44 * s44);
+        const double i1 = 1.0 / s44;
         double acc = 0.0;
 #pragma unroll 2
         for (int f = 0; f < n_times; ++f) {
             const double d = times[f] - G.mu[3];
-            const double p2 = (d * d * i2 - i1) * exp(d * d * i0);
+            const double q = d * i1;   // q^2 overflows only where d^2 / S44^2 does (1 / S44^2 would before)
+            const double p2 = (q * q - i1) * exp(-0.5 * d * q);
             acc += 1.0 + exp(-2.0 * fabs(p2));
         }
         s = (float)acc;
