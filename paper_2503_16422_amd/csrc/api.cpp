@@ -881,8 +881,9 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
     int64_t *counts = S->counts.as<int64_t>();
 
     const int64_t pre_blocks = (n_total + kPreprocessBlock - 1) / kPreprocessBlock;
-    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * 7 * (size_t)pre_blocks));
-    uint32_t *samples = S->vis_count.as<uint32_t>(), *block_range = samples + 4 * pre_blocks;
+    const size_t sample_words = (size_t)V * kSampleBlocks * 4;
+    HIP_TRY(ensure(S->vis_count, sizeof(uint32_t) * (sample_words + 3 * (size_t)pre_blocks)));
+    uint32_t *samples = S->vis_count.as<uint32_t>(), *block_range = samples + sample_words;
     uint32_t *vis_count = block_range + 2 * pre_blocks;
     PreprocOut po{S->rec.as<Rec2D>(), S->depth_key.as<uint64_t>(), S->rect.as<int32_t>(), S->tiles.as<uint32_t>(),
                   S->visible.as<uint8_t>(), vis_count, block_range, samples, S->bucket.as<uint32_t>(),

@@ -36,12 +36,21 @@ struct PreprocOut {
     uint8_t *visible;    // [P]
     uint32_t *vis_count; // [ceil(P / kPreprocessBlock)] visible entries per workgroup, or NULL
     uint32_t *block_range;   // [2 ceil(P / kPreprocessBlock)] [min, max] float32 depth bits of a workgroup's visible entries
-    uint32_t *samples;       // [4 ceil(P / kPreprocessBlock)], 16-byte aligned: those of one visible entry of each wavefront (~0: none)
+    uint32_t *samples;       // [V][kSampleBlocks][4], 16-byte aligned: sampled keys (see sample_block)
     uint32_t *clear;     // [n_clear] words the launch zeroes
     int64_t n_clear;
 };
 // Entries per preprocess workgroup (its visible counts feed the compaction's scan).
 constexpr int kPreprocessBlock = 256;
+// Sampled keys of a view: up to kSampleBlocks times four, the s-th four from
+// workgroup sample_block(s, n) of the view's n (one at or past n: not written),
+// one visible entry of each of its wavefronts (~0: none).
+constexpr int kSampleBlocks = 512;
+__host__ __device__ inline uint32_t sample_stride(uint32_t n) { return (n + kSampleBlocks - 1) / kSampleBlocks; }
+__host__ __device__ inline uint32_t sample_block(uint32_t s, uint32_t n) {
+    const uint32_t stride = sample_stride(n);
+    return stride > 1u ? s * stride + ((s * 2654435761u) >> 12) % stride : s;
+}
 // V == 1: `one` is passed by value and n_dev may hold the device count.
 // Otherwise `table` is a device array of V views with host-known counts and
 // n_total is a multiple of kViewChunk.

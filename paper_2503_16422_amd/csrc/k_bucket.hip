@@ -75,7 +75,7 @@ __device__ __forceinline__ int64_t count_of(const int64_t *n_dev, int64_t n_max)
 // depth, the slabs 6 and 54 ms; dividing the whole range evenly: the slabs 5 and
 // 42 ms.)
 constexpr int kBins = 128, kSub = 64, kHeavy = 8;
-constexpr int kSampleBlocks = 2 * kNT;
+static_assert(kSampleBlocks == 2 * kNT, "two of them a thread");
 struct MapTables {
     uint32_t base[kBins + 1];             // buckets before a bin
     uint32_t heavy[kBins];                // a heavy bin's place in sub, or ~0
@@ -176,7 +176,7 @@ struct SrcViews {
     const uint8_t *visible;
     const uint64_t *depth_key;
     const uint32_t *block_range;   // [min, max] key of each preprocess workgroup's visible entries
-    const uint32_t *samples;       // [4] keys of each preprocess workgroup (~0: none), or null: its range's ends
+    const uint32_t *samples;       // of each view, or null: the ends of the sampled workgroups' ranges
     const int64_t *n_dev;          // one view (table null): device count
     int64_t n_max;
     const ViewDesc *table;
@@ -206,16 +206,15 @@ struct SrcViews {
         const int64_t base = table ? table[w.v].p_off : 0;
         const int64_t n = table ? table[w.v].n_proc : count_of(n_dev, n_max);
         const int64_t b0 = base / kPreprocessBlock, b1 = (base + n + kPreprocessBlock - 1) / kPreprocessBlock;
-        const uint32_t stride = (uint32_t)((b1 - b0 + kSampleBlocks - 1) / kSampleBlocks);
         *sampled = 4u * (uint32_t)min(b1 - b0, (int64_t)kSampleBlocks);
 #pragma unroll
         for (int q = 0; q < kSampleBlocks / kNT; ++q) {
             const uint32_t s = threadIdx.x + (uint32_t)q * kNT;
-            const int64_t b = b0 + (int64_t)s * stride + ((s * 2654435761u) >> 12) % stride;
+            const int64_t b = b0 + sample_block(s, (uint32_t)(b1 - b0));
             uint4 k = make_uint4(~0u, ~0u, ~0u, ~0u);
             if (b < b1) {
                 if (samples) {
-                    k = reinterpret_cast<const uint4 *>(samples)[b];
+                    k = reinterpret_cast<const uint4 *>(samples)[(size_t)w.v * kSampleBlocks + s];
                 } else if (block_range[2 * b] <= block_range[2 * b + 1]) {
                     k.x = block_range[2 * b];
                     k.y = block_range[2 * b + 1];

@@ -142,7 +142,6 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
         if (t == 0) {
             a.out.block_range[2 * blockIdx.x] = ~0u;
             a.out.block_range[2 * blockIdx.x + 1] = 0u;
-            reinterpret_cast<uint4 *>(a.out.samples)[blockIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
             if (a.out.vis_count) a.out.vis_count[blockIdx.x] = 0u;
         }
         return;
@@ -150,12 +149,16 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
     bool vis = false;
     int4 r4 = make_int4(0, 0, -1, -1);
     CullEllipse ell = {};
-    uint32_t key = 0;
+    uint32_t key = 0, view = 0, first_block = 0;
+    int64_t n_view = P;
     if (!a.table) {
         if (j < P) vis = preprocess_one(a.one, j, a, &r4, &ell, &key);
     } else {
         // the workgroup's entries belong to one view; the last ones of its chunks may be padding
-        const ViewDesc &vd = a.table[__builtin_amdgcn_readfirstlane((int)a.chunk_view[blockIdx.x / (kViewChunk / kBlock)])];
+        view = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.chunk_view[blockIdx.x / (kViewChunk / kBlock)]);
+        const ViewDesc &vd = a.table[view];
+        n_view = vd.n_proc;
+        first_block = (uint32_t)(vd.p_off / kBlock);
         if (j - vd.p_off < vd.n_proc) vis = preprocess_one(vd, j, a, &r4, &ell, &key);
     }
     if (j < P) a.out.visible[j] = vis ? 1 : 0;
@@ -171,11 +174,15 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
             s_range[2 * wave_id() + 1] = hi;
         }
         // a sample of the wavefront's depths: its first visible lane from a hashed one on
-        const uint64_t m = __ballot(vis);
-        const uint32_t at = (uint32_t)blockIdx.x * (kBlock / 64) + (uint32_t)wave_id();
-        const int from = (int)((at * 2654435761u) >> 26);
-        const uint64_t turned = from ? m >> from | m << (64 - from) : m;
-        if (lane_id() == (m ? (__builtin_ctzll(turned) + from) & 63 : 0)) a.out.samples[at] = m ? key : ~0u;
+        const uint32_t n_blocks = (uint32_t)((n_view + kBlock - 1) / kBlock), b = (uint32_t)blockIdx.x - first_block;
+        const uint32_t s = b / sample_stride(n_blocks);
+        if (sample_block(s, n_blocks) == b) {                // uniform
+            const uint64_t m = __ballot(vis);
+            const uint32_t at = (view * kSampleBlocks + s) * (kBlock / 64) + (uint32_t)wave_id();
+            const int from = (int)((at * 2654435761u) >> 26);
+            const uint64_t turned = from ? m >> from | m << (64 - from) : m;
+            if (lane_id() == (m ? (__builtin_ctzll(turned) + from) & 63 : 0)) a.out.samples[at] = m ? key : ~0u;
+        }
     }
     const int tw = a.rp.tile_w, th = a.rp.tile_h;
     uint32_t rows = 0, direct = 0;

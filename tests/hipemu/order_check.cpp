@@ -38,7 +38,7 @@ int main() {
         }
         std::vector<uint8_t> vis(n);
         std::vector<uint64_t> dk(n), offsets(n, 77);
-        std::vector<uint32_t> tiles(n), range(2 * blocks, 0u), samples(4 * blocks, ~0u), ref;
+        std::vector<uint32_t> tiles(n), range(2 * blocks, 0u), samples(4 * kSampleBlocks, ~0u), ref;
         for (int64_t b = 0; b < blocks; ++b) range[2 * b] = ~0u;
         for (int64_t j = 0; j < n; ++j) {
             std::memcpy(&dk[j], &z[j], 8);
@@ -50,8 +50,8 @@ int main() {
             uint32_t *r = &range[2 * (j / kPreprocessBlock)];
             r[0] = std::min(r[0], key);
             r[1] = std::max(r[1], key);
-            uint32_t &s = samples[j / 64];                     // some visible entry of the wavefront
-            if (s == ~0u || rng() % 8 == 0) s = key;
+            uint32_t &s = samples[j / 64];                     // some visible entry of the wavefront (every
+            if (s == ~0u || rng() % 8 == 0) s = key;           // workgroup is sampled: fewer than kSampleBlocks)
         }
         std::sort(ref.begin(), ref.end(), [&](uint32_t a, uint32_t b) { return std::tie(dk[a], a) < std::tie(dk[b], b); });
         size_t words = 0, clear = 0;
