@@ -59,7 +59,7 @@ def test_adjoint_without_room_for_float64_lines():
                 ctx.backward(st, rgb, model, g)
             torch.cuda.synchronize()
             taken = before - torch.cuda.mem_get_info()[0]
-        assert (taken < 128 * n) == small
+        assert (taken < 64 * n) == small           # 36 bytes an entry, or 128
         out += [{k: v[..., :kept].clone() for k, v in g.items()} for g in grads]
         st.release()
         ctx.close()
