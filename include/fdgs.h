@@ -466,9 +466,9 @@ FDGS_API fdgs_status fdgs_check_overflow(fdgs_ctx *ctx, hipStream_t stream);
  */
 enum {
     FDGS_STAGE_PREPROCESS = 0,   /* slice + project + SH + footprint        */
-    FDGS_STAGE_COMPACT = 1,      /* visible-set scan and scatter             */
-    FDGS_STAGE_DEPTH_SORT = 2,   /* depth radix sort + tie fix               */
-    FDGS_STAGE_OFFSETS = 3,      /* instance offsets (scan)                  */
+    FDGS_STAGE_COMPACT = 1,      /* visible-set scan and scatter (radix path, kept states) */
+    FDGS_STAGE_DEPTH_SORT = 2,   /* depth order and offsets by buckets, or radix sort + tie fix */
+    FDGS_STAGE_OFFSETS = 3,      /* instance offsets (scan; radix path)      */
     FDGS_STAGE_DUPLICATE = 4,    /* tile-key emission                        */
     FDGS_STAGE_TILE_SORT = 5,    /* tile radix sort                          */
     FDGS_STAGE_RANGES = 6,       /* tile ranges (and the longest-first order) */

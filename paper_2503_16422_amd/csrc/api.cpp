@@ -158,6 +158,7 @@ constexpr int32_t kDefaultPpt = 2;
 // is the model's size, since a mask may keep all of it (3M, 27% kept: 128 and 153
 // us; 60%: 367 and 186; all: 760 and 239).
 constexpr int64_t kBucketMaxN = int64_t(1) << 20;
+
 // Several views of one forward pass: device copies of their descriptions and of
 // the view of each chunk of entries, the largest processed count and their sum
 // (without the padding of the chunks).
@@ -898,7 +899,8 @@ fdgs_status run_forward(fdgs_ctx *ctx, fdgs_state *S, const ViewDesc *one, const
         if (need_state) HIP_TRY(ensure(S->vis_pos, sizeof(uint32_t) * n_max));
         HIP_TRY(compact_visible(S->visible.as<uint8_t>(), S->depth_key.as<uint64_t>(), n_dev, n_max, counts + 0,
                                 by_buckets ? nullptr : S->order_k.as<uint32_t>(),
-                                by_buckets ? nullptr : S->order_v.as<uint32_t>(), need_state ? S->vis_pos.as<uint32_t>() : nullptr, nullptr, 0, nullptr, S->scratch.p,
+                                by_buckets ? nullptr : S->order_v.as<uint32_t>(),
+                                need_state ? S->vis_pos.as<uint32_t>() : nullptr, nullptr, 0, nullptr, S->scratch.p,
                                 stream, vis_count));
     }
     uint32_t *ov = nullptr;

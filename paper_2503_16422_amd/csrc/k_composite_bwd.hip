@@ -51,14 +51,14 @@ struct BwdArgs {
 // add them into the tile's LDS accumulators with one instruction.  After each
 // batch the sums leave the tile as gradients, nine consecutive lanes to the
 // nine values of a Gaussian, which share one 128-byte line of g2d: an atomic
-// instruction then touches seven lines, where a thread per Gaussian touched 64
-// lines nine times.  Over the tiles the gradients add up in float64: a large
-// footprint's terms cancel over hundreds of tiles, and the parameter adjoint
-// amplifies what float32 sums in arbitrary order leave.  (Fine-tuning frame, 200k Gaussians, 16x16 tiles: adjoint
-// 500 -> 245 us, of which the global adds took 190 and the LDS adds 68; training
-// view, 500k, 32x32: 311 -> 224 us.)  A wavefront walks only the records whose
-// footprint ellipse reaches its cell: the others have alpha below alpha_min at
-// every one of its pixels and contribute nothing.
+// instruction then touches eight or nine lines, where a thread per Gaussian
+// touched 64 lines nine times.  Over the tiles the gradients add up in float64: a
+// large footprint's terms cancel over hundreds of tiles, and the parameter adjoint
+// amplifies what float32 sums in arbitrary order leave.  (Fine-tuning frame, 200k
+// Gaussians, 16x16 tiles: adjoint 500 -> 238 us, of which the global adds took 190
+// and the LDS adds 68; training view, 500k, 32x32: 311 -> 227 us.)  A wavefront
+// walks only the records whose footprint ellipse reaches its cell: the others have
+// alpha below alpha_min at every one of its pixels and contribute nothing.
 template <int CTRL>
 __device__ __forceinline__ float dpp_of(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
