@@ -174,7 +174,8 @@ __global__ void __launch_bounds__(kBlock) preprocess_kernel(PreArgs a) {
             s_range[2 * wave_id() + 1] = hi;
         }
         // a sample of the wavefront's depths: its first visible lane from a hashed one on
-        const uint32_t n_blocks = (uint32_t)((n_view + kBlock - 1) / kBlock), b = (uint32_t)blockIdx.x - first_block;
+        // (an empty view counts as one workgroup; those of the padding write slots that are not read)
+        const uint32_t n_blocks = max((uint32_t)((n_view + kBlock - 1) / kBlock), 1u), b = (uint32_t)blockIdx.x - first_block;
         const uint32_t s = b / sample_stride(n_blocks);
         if (sample_block(s, n_blocks) == b) {                // uniform
             const uint64_t m = __ballot(vis);
